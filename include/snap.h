@@ -401,8 +401,8 @@ int snap_conservation_sums_noalloc(const snap_grid* g, void* q, double* sums_hos
 /*
  * Ensemble of independent 2-D (ny == 1) domains advanced by one SSP-RK3 step
  * each (Sec. 4.3), with per-member grids, states and time steps. Every stage
- * is one batched ghost-fill launch and one persistent stage launch for all
- * members: `nblocks` workgroups walk the (member, tile) work items round-robin
+ * is one persistent stage launch for all members (ghost values are read at
+ * their sources): `nblocks` workgroups walk the (member, tile) work items round-robin
  * (0 = as many as fit on the device at once). Members must share dtype,
  * ntracer, equation of state and Riemann solver (the passive gas or the
  * mixture; LMARS or HLLC), else SNAP_E_INVALID; 3-D members, and members

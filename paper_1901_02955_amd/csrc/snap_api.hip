@@ -511,15 +511,14 @@ int check_batch(const snap_grid* gs, int n) {
 }
 
 struct BatchLayout {
-  size_t descs, ghosts, first, members, total;
+  size_t descs, first, members, total;
   std::vector<size_t> q1, q2;
 };
 
 BatchLayout batch_layout(const snap_grid* gs, int n) {
   BatchLayout L;
   L.descs = 0;
-  L.ghosts = align256((size_t)3 * n * sizeof(StageArgs));
-  L.first = L.ghosts + align256((size_t)3 * n * sizeof(GhostDesc));
+  L.first = align256((size_t)3 * n * sizeof(StageArgs));
   L.members = L.first + align256((size_t)(n + 1) * sizeof(int));
   size_t off = L.members;
   L.q1.resize(n);
@@ -676,10 +675,10 @@ int rk3_stages(const snap_grid* g, void* q, double dt, const unsigned long long*
   a.smax = smax;
   a.cfl = cfl;
   a.rhs_mode = 0;
-  // The 3-D stage kernels without tracers read the ghost cells they need at
-  // their sources, so their input needs no fill; the sedimentation kernel
-  // still reads z ghosts.
-  if (is3d(g) && !a.sed.on && ghosts_in_place(g->ntracer)) a.ghost |= GF_ON;
+  // The 3-D stage kernels without tracers and the 2-D ones read the ghost cells
+  // they need at their sources, so their input needs no fill; the
+  // sedimentation kernels still read z ghosts.
+  if (!a.sed.on && (!is3d(g) || ghosts_in_place(g->ntracer))) a.ghost |= GF_ON;
   auto prepare = [&](void* x) { return (a.ghost & GF_ON) ? SNAP_OK : fill(g, x, st); };
   // Q1 = Q + dt R(Q)
   if ((r = prepare(q))) return r;
@@ -715,11 +714,10 @@ int rk3_stages(const snap_grid* g, void* q, double dt, const unsigned long long*
   return ok();
 }
 
-// Grids whose last stage can reduce the next step's signal speed itself
-// (fused_speed in the kernels: no tracers, 3-D, ghosts read in place, i.e. no
-// sedimentation).
+// Grids whose last stage can reduce the next step's signal speed itself (3-D:
+// the kernels without tracers; 2-D: those of the passive gas).
 bool fused_speed_ok(const snap_grid* g) {
-  return is3d(g) && ghosts_in_place(g->ntracer) && !sediment_of(g).on;
+  return is3d(g) ? ghosts_in_place(g->ntracer) : !uses_mixture(g);
 }
 
 // The 256 bytes after the two padded stage states of the SNAP_OP_RK3_CFL
@@ -943,9 +941,8 @@ int snap_rk3_step_batched(const snap_grid* gs, int n, void* const* q, const doub
   thread_local std::vector<char> host;
   host.assign(L.members, 0);
   StageArgs* hd = reinterpret_cast<StageArgs*>(host.data() + L.descs);
-  GhostDesc* hg = reinterpret_cast<GhostDesc*>(host.data() + L.ghosts);
   int* hf = reinterpret_cast<int*>(host.data() + L.first);
-  long long items = 0, max_ghosts = 0;
+  long long items = 0;
   for (int m = 0; m < n; ++m) {
     const snap_grid* g = &gs[m];
     StageArgs a = stage_args(g);
@@ -955,6 +952,7 @@ int snap_rk3_step_batched(const snap_grid* gs, int n, void* const* q, const doub
     a.tz = g->nz;
     a.dt = dt_host[m];
     a.rhs_mode = 0;
+    a.ghost |= GF_ON;   // the 2-D kernels read ghosts at their sources
     void* q1 = base + L.q1[m];
     void* q2 = base + L.q2[m];
     StageArgs s1 = a, s2 = a, s3 = a;
@@ -964,14 +962,8 @@ int snap_rk3_step_batched(const snap_grid* gs, int n, void* const* q, const doub
     hd[m] = s1;
     hd[n + m] = s2;
     hd[2 * n + m] = s3;
-    const GhostArgs ga = ghost_args(g);
-    hg[m] = GhostDesc{ga, q[m]};
-    hg[n + m] = GhostDesc{ga, q1};
-    hg[2 * n + m] = GhostDesc{ga, q2};
     hf[m] = (int)items;
     items += (long long)a.tiles_x * a.tiles_y;
-    const long long ng = 6LL * ga.nyp * ga.nxp + (long long)ga.nz * ga.ny * 6;
-    max_ghosts = ng > max_ghosts ? ng : max_ghosts;
   }
   if (items > (1LL << 30)) return fail(SNAP_E_INVALID, "too many tiles in the batch");
   hf[n] = (int)items;
@@ -988,11 +980,8 @@ int snap_rk3_step_batched(const snap_grid* gs, int n, void* const* q, const doub
   }
   if (nb > items) nb = (int)items;
   const StageArgs* dd = reinterpret_cast<const StageArgs*>(base + L.descs);
-  const GhostDesc* dg = reinterpret_cast<const GhostDesc*>(base + L.ghosts);
   const int* df = reinterpret_cast<const int*>(base + L.first);
   for (int s = 0; s < 3; ++s) {
-    if (launch_fill_ghosts_batched(dtype, dg + s * n, n, max_ghosts, st))
-      return device_fail("batched ghost fill launch");
     if (launch_stage2d_batched(dtype, nt, variant, form, dd + s * n, df, n, nb, st))
       return device_fail("batched stage launch");
   }

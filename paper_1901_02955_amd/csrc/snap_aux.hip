@@ -88,13 +88,6 @@ __global__ void k_fill_ghosts(T* __restrict__ q, GhostArgs a) {
   fill_ghosts_all<T>(q, a);
 }
 
-// All members of an ensemble: member blockIdx.y.
-template <typename T>
-__global__ void k_fill_ghosts_batched(const GhostDesc* __restrict__ d) {
-  const GhostDesc g = d[blockIdx.y];
-  fill_ghosts_all<T>(static_cast<T*>(g.q), g.a);
-}
-
 // ---------------------------------------------------------------------------
 // CFL: per-cell signal speed sum_d (|u_d| + c) / dx_d in double precision
 // (each term multiplied by the reciprocal spacing 1 / dx_d),
@@ -295,18 +288,6 @@ int launch_fill_ghosts(int dtype, void* q, const GhostArgs& a, hipStream_t st) {
   else
     hipLaunchKernelGGL(k_fill_ghosts<float>, dim3((unsigned)nb), dim3(256), 0, st,
                        static_cast<float*>(q), a);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_fill_ghosts_batched(int dtype, const GhostDesc* d, int n, long long max_ghosts,
-                               hipStream_t st) {
-  long long nb = (max_ghosts + 255) / 256;
-  if (nb > 4096) nb = 4096;
-  if (nb < 1) nb = 1;
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_fill_ghosts_batched<double>, dim3((unsigned)nb, n), dim3(256), 0, st, d);
-  else
-    hipLaunchKernelGGL(k_fill_ghosts_batched<float>, dim3((unsigned)nb, n), dim3(256), 0, st, d);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

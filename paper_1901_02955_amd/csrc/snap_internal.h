@@ -16,12 +16,6 @@ struct GhostArgs {
   long long sy, sz, sv;
 };
 
-// Ghost fill of one ensemble member.
-struct GhostDesc {
-  GhostArgs a;
-  void* q;
-};
-
 struct CflArgs {
   int nx, ny, nz, gy, d3;
   long long sy, sz, sv;
@@ -118,8 +112,6 @@ int occupancy_sed_f32(int ntracer);
 int launch_stage_hllc_f64(int ntracer, bool d3, StageArgs a, int nblocks, hipStream_t st);
 int launch_stage_hllc_f32(int ntracer, bool d3, StageArgs a, int nblocks, hipStream_t st);
 int launch_fill_ghosts(int dtype, void* q, const GhostArgs& a, hipStream_t st);
-int launch_fill_ghosts_batched(int dtype, const GhostDesc* d, int n, long long max_ghosts,
-                               hipStream_t st);
 
 // Batched (ensemble) 2-D stage kernel: tile variant v of the element type.
 constexpr int BATCH_VARIANTS = 6;
