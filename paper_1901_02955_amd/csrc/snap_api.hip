@@ -290,7 +290,8 @@ bool pass_weights(const snap_grid* g, int passes, double* w) {
 // Tiling of the stage launch; returns the number of workgroups.
 int stage_tiling(const snap_grid* g, StageArgs& a) {
   const bool d3 = is3d(g);
-  const TileShape t = g->dtype == SNAP_F64 ? tile_f64(nvar_of(g)) : tile_f32(nvar_of(g));
+  const TileShape t = g->dtype == SNAP_F64 ? tile_f64(nvar_of(g), d3, uses_mixture(g))
+                                           : tile_f32(nvar_of(g), d3, uses_mixture(g));
   a.tiles_x = (g->nx + t.tx - 1) / t.tx;
   if (!d3) {
     a.tiles_y = (g->nz + t.ty - 1) / t.ty;
@@ -329,6 +330,7 @@ int stage_tiling(const snap_grid* g, StageArgs& a) {
   // dispatch pass c, and its level range is sized by that pass's speed.
   int cus = 0;
   resident_slots(g, &cus);
+  a.low = (long long)tiles * a.nchunk <= cus ? 1 : 0;
   double w[SNAP_MAX_PASSES];
   a.pass_map = 0;
   if (tiles == cus && tiles % 8 == 0 && (long long)tiles * a.nchunk == slots &&

@@ -291,6 +291,38 @@ __device__ __forceinline__ void weno5_cell(T a, T b, T c, T d, T e, T eps, bool 
   }
 }
 
+// The left state at face j+1/2 alone (weno5_cell's qm); with the stencil given
+// in reverse order, e, d, c, b, a, it is the right state at face j-1/2 (qp: the
+// two are mirror images). For a quantity that only the upwind side of a face
+// carries, one such value per face replaces both values of every cell.
+template <typename T>
+__device__ __forceinline__ T weno5_face(T a, T b, T c, T d, T e, T eps, bool linear) {
+  const T da = a - c, db = b - c, dd = d - c, de = e - c;
+  const T u1 = db + dd, v1 = db - dd;
+  const T A0 = fma(T(2.0 / 3.0), da, T(-7.0 / 3.0) * db);
+  const T A1 = fma(T(-3), v1, u1);
+  const T A2 = fma(T(5), dd, -de);
+  if (linear) return fma(T(0.05), (A0 + A1) + A2, c);
+  const T k13 = T(13) / T(3), eps4 = T(4) * eps;
+  const T u0 = fma(T(-2), db, da), v0 = fma(T(-4), db, da);
+  const T u2 = fma(T(-2), dd, de), v2 = fma(T(-4), dd, de);
+  T s0 = fma(v0, v0, fma(k13 * u0, u0, eps4));
+  T s1 = fma(v1, v1, fma(k13 * u1, u1, eps4));
+  T s2 = fma(v2, v2, fma(k13 * u2, u2, eps4));
+  if constexpr (sizeof(T) == 4) {
+    const float mx = fmaxf(fmaxf(s0, s1), s2);
+    const float sc = __uint_as_float(0x7F000000u - __float_as_uint(mx));
+    s0 *= sc;
+    s1 *= sc;
+    s2 *= sc;
+  }
+  const T q0 = s0 * s0, q1 = s1 * s1, q2 = s2 * s2;
+  const T t0 = q1 * q2, t1 = q0 * q2, t2 = q0 * q1;
+  const T den = fma(T(2), t0, fma(T(6), t2, T(12) * t1));
+  const T num = fma(t0, A0, fma(t1, A1, t2 * A2));
+  return fma(num, rcp_fast(den), c);
+}
+
 // ---------------------------------------------------------------------------
 // LMARS flux at one face (Sec. 4.1, eqs. rp and ru), returned DOUBLED: f is
 // twice the face flux (the callers scale the flux differences by half the
@@ -310,10 +342,11 @@ __device__ __forceinline__ void weno5_cell(T a, T b, T c, T d, T e, T eps, bool 
 // The advected vector (rho, rho u, rho v, rho w, E + p, rho q_i) comes from the
 // upwind side (left if u* > 0, else right; at u* == 0 every advective term is
 // zero, so the side does not matter), with E + p = p gamma / (gamma - 1) +
-// rho |u|^2 / 2; 2 p* is added to the normal momentum flux.
+// rho |u|^2 / 2; 2 p* is added to the normal momentum flux. left: the upwind
+// side, whose tracer fractions the mass flux f[0] carries.
 template <typename T, int NV>
 __device__ __forceinline__ void lmars_flux(const T (&xl)[NV], const T (&xr)[NV], int nrm, T rref,
-                                           T pref, T gamma, T inv_gm1, T (&f)[NV]) {
+                                           T pref, T gamma, T inv_gm1, T (&f)[NV], bool& left) {
   const T rl = rref + xl[0], rr = rref + xr[0];
   const T pl = pref + xl[4], pr = pref + xr[4];
   const T unl = xl[nrm], unr = xr[nrm];
@@ -322,7 +355,7 @@ __device__ __forceinline__ void lmars_flux(const T (&xl)[NV], const T (&xr)[NV],
   const T RC = (rl + rr) * (cl + cr);
   const T pstar2 = fma(T(-0.25) * RC, unr - unl, xl[4] + xr[4]);
   const T ustar2 = fma(T(-4) * (xr[4] - xl[4]), rcp_fast(RC), unl + unr);
-  const bool left = ustar2 > T(0);
+  left = ustar2 > T(0);
   const T rs = left ? rl : rr;
   const T ps = left ? pl : pr;
   const T us = left ? xl[1] : xr[1];
@@ -349,9 +382,10 @@ __device__ __forceinline__ void lmars_flux(const T (&xl)[NV], const T (&xr)[NV],
 // velocities, E_K/rho_K + (S* - u_K)(S* + p_K / d_K), q_K). Face states and
 // references as for lmars_flux; the normal momentum flux carries the
 // perturbation pressure (the full flux minus the face reference pressure).
+// Every tracer flux is q_K f[0]; left: the side K.
 template <typename T, int NV>
 __device__ __forceinline__ void hllc_flux(const T (&xl)[NV], const T (&xr)[NV], int nrm, T rref,
-                                          T pref, T gamma, T inv_gm1, T (&f)[NV]) {
+                                          T pref, T gamma, T inv_gm1, T (&f)[NV], bool& left) {
   const T rl = rref + xl[0], rr = rref + xr[0];
   const T pl = pref + xl[4], pr = pref + xr[4];
   const T unl = nrm == 1 ? xl[1] : (nrm == 2 ? xl[2] : xl[3]);
@@ -362,7 +396,7 @@ __device__ __forceinline__ void hllc_flux(const T (&xl)[NV], const T (&xr)[NV], 
   const T dl = rl * (SL - unl), dr = rr * (SR - unr);
   const T Ss = (pr - pl + dl * unl - dr * unr) * rcp_fast(dl - dr);
   // the side whose flux (plain or star) is taken, and whether in the star region
-  const bool left = SL >= T(0) || Ss >= T(0);
+  left = SL >= T(0) || Ss >= T(0);
   const bool star = !(SL >= T(0)) && (left || SR > T(0));
   const T rk = left ? rl : rr, pk = left ? pl : pr, ppk = left ? xl[4] : xr[4];
   const T uk = left ? xl[1] : xr[1], vk = left ? xl[2] : xr[2], wk = left ? xl[3] : xr[3];

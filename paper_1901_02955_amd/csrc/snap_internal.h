@@ -66,12 +66,13 @@ struct SumArgs {
   const double* pbar_c;
 };
 
-// Tile shape of the stage kernels for an element size and variable count.
+// Tile shape of the stage kernels for an element size, variable count, 2-D or
+// 3-D, and equation of state.
 struct TileShape {
   int tx, ty;
 };
-TileShape tile_f64(int nv);
-TileShape tile_f32(int nv);
+TileShape tile_f64(int nv, bool d3, bool mix);
+TileShape tile_f32(int nv, bool d3, bool mix);
 int occupancy_f64(int ntracer, bool d3);
 int occupancy_f32(int ntracer, bool d3);
 int occupancy_mix_f64(int ntracer, bool d3);

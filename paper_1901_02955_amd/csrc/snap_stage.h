@@ -91,6 +91,8 @@ struct StageArgs {
   // that time step is not finite and positive, i.e. the reduced state had a
   // non-finite or non-positive density or pressure somewhere.
   unsigned long long* state_flag;
+  // 3-D only: at most one workgroup per compute unit (Stage3DShape's LOW)
+  int low;
   // 1: q holds rho - rhobar_k and E - pbar_k / (gamma - 1) (perturbation
   // storage, passive tracers only); 0: the full conserved state.
   int pert;
@@ -226,18 +228,31 @@ constexpr double flux_scale() {
 }
 
 // Face flux of the kernel's Riemann solver (LMARS, or HLLC with passive
-// tracers) and equation of state, times flux_scale<MIX, HLLC>().
+// tracers) and equation of state, times flux_scale<MIX, HLLC>(). left: the
+// upwind side (not set under the mixture).
 template <typename T, int NV, bool MIX, bool HLLC>
 __device__ __forceinline__ void riemann_flux(const T (&xl)[NV], const T (&xr)[NV], int nrm,
                                              T rref, T pref, T gamma, T inv_gm1, T gm1,
-                                             const Mixture& mx, T (&f)[NV]) {
+                                             const Mixture& mx, T (&f)[NV], bool& left) {
   static_assert(!(MIX && HLLC), "HLLC takes passive tracers");
   if constexpr (HLLC)
-    hllc_flux<T, NV>(xl, xr, nrm, rref, pref, gamma, inv_gm1, f);
+    hllc_flux<T, NV>(xl, xr, nrm, rref, pref, gamma, inv_gm1, f, left);
   else if constexpr (MIX)
     lmars_flux_mix<T, NV>(xl, xr, nrm, rref, pref, gm1, mx, f);
   else
-    lmars_flux<T, NV>(xl, xr, nrm, rref, pref, gamma, inv_gm1, f);
+    lmars_flux<T, NV>(xl, xr, nrm, rref, pref, gamma, inv_gm1, f, left);
+}
+
+// Variables whose in-plane face states are reconstructed on both sides: all of
+// them under the mixture, whose flux needs both sides' fractions; the five
+// dynamic ones with passive tracers, whose flux is the mass flux times the
+// upwind side's fraction (phase L reconstructs that one value per face). In
+// 3-D and single precision one tracer keeps both sides: it gains no wave, and
+// saves the barrier before the last fluxes (686 -> 678 us per step of
+// 256 x 192 x 96).
+template <typename T, int NV, bool MIX, bool D3>
+constexpr int two_sided() {
+  return MIX || (D3 && sizeof(T) == 4 && NV == 6) ? NV : 5;
 }
 
 // Output of one interior cell: either R itself or the stage combination (the
@@ -377,17 +392,18 @@ constexpr bool reconstruct_prefetch() {
 // variables while the others wait at the barrier. Without SPLIT they are a
 // last round of whole items, which needs fewer registers: the callers keep
 // that form where the split would cost a wave per SIMD or add spills.
-template <typename T, int NV, int TX, int TY, bool SPLIT = true>
+// ND: the variables reconstructed (the first ND of NV, two_sided).
+template <typename T, int NV, int ND, int TX, int TY, bool SPLIT = true>
 __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
                                                   bool linear,
-                                                  T (&QP)[PlaneItems<TX, TY>::RREG][NV]) {
+                                                  T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
   using I = PlaneItems<TX, TY>;
   constexpr bool RPF = reconstruct_prefetch<T, NV>();
   constexpr int PV = (TY + 6) * (TX + 6);   // plane stride between variables
   constexpr int FXV = TY * (TX + 1), FYV = (TY + 1) * TX;
   constexpr int NSP = I::NR - I::RREG * I::NTHR;   // cells left after the RREG rounds
   if constexpr (SPLIT && NSP > 0) {
-    constexpr int NSUB = NSP * NV;
+    constexpr int NSUB = NSP * ND;
     const int t0 = item_thread<I::NTHR>();
 #pragma unroll
     for (int m = 0; m < (NSUB + I::NTHR - 1) / I::NTHR; ++m) {
@@ -426,17 +442,17 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
       T* dst = xa ? &S.FX[0][jj][ii + 1] : &S.FY[0][jj + 1][ii];
       const int dv = xa ? FXV : FYV;
       const bool put = xa ? ii < w : jj < h;
-      T qp[NV];
+      T qp[ND];
       T cur[5];
       if constexpr (RPF) {
 #pragma unroll
         for (int m = 0; m < 5; ++m) cur[m] = src[m * st];
       }
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
+      for (int v = 0; v < ND; ++v) {
         T nxt[5];
         if constexpr (RPF) {
-          if (v + 1 < NV) {
+          if (v + 1 < ND) {
 #pragma unroll
             for (int m = 0; m < 5; ++m) nxt[m] = src[(v + 1) * PV + m * st];
           }
@@ -449,14 +465,14 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
         if (put) dst[v * dv] = qm;
         SNAP_VAR_FENCE();
         if constexpr (RPF) {
-          if (v + 1 < NV) {
+          if (v + 1 < ND) {
 #pragma unroll
             for (int m = 0; m < 5; ++m) cur[m] = nxt[m];
           }
         }
       }
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
+      for (int v = 0; v < ND; ++v) {
         if (r < I::RREG)
           QP[r < I::RREG ? r : 0][v] = qp[v];
         else
@@ -471,12 +487,35 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
 // sref(face index). SNRM is the index of the second axis's velocity; the flux
 // is called in two branches, each with a constant normal, so that picking the
 // normal velocity and adding p* need no selects over the velocity components.
-template <typename T, int NV, int TX, int TY, int SNRM, bool MIX, bool HLLC, typename XRef,
-          typename SRef>
-__device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int h,
-                                            T gamma, T inv_gm1, T gm1, const Mixture& mx,
-                                            XRef xref, SRef sref,
-                                            const T (&QP)[PlaneItems<TX, TY>::RREG][NV]) {
+// The upwind value of one variable at a face between cells c-1 and c of a line
+// of the plane: cells c-3 .. c+1 in order from the left side, c+2 .. c-2 from
+// the right, so the side only picks the five addresses (lo: cell c-3, stride st).
+template <typename T>
+struct UpwindStencil {
+  const T* p[5];
+  __device__ __forceinline__ UpwindStencil(const T* lo, int st, bool left) {
+    const int step = left ? st : -st;
+    p[0] = lo + (left ? 0 : 5 * st);
+#pragma unroll
+    for (int m = 1; m < 5; ++m) p[m] = p[m - 1] + step;
+  }
+  __device__ __forceinline__ T face(int off, T eps, bool linear) const {
+    return weno5_face<T>(p[0][off], p[1][off], p[2][off], p[3][off], p[4][off], eps, linear);
+  }
+};
+
+// Passive tracers: once a face's flux is known, so is its upwind side, and the
+// item reconstructs each tracer there from the plane (UpwindStencil) and
+// multiplies by the mass flux. Against the
+// two-sided reconstruction of every cell it saves a fifth of the WENO
+// instructions, the face states' way through LDS and the right states'
+// registers.
+template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool MIX, bool HLLC,
+          typename XRef, typename SRef>
+__device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
+                                            bool linear, T gamma, T inv_gm1, T gm1,
+                                            const Mixture& mx, XRef xref, SRef sref,
+                                            const T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
   using I = PlaneItems<TX, TY>;
 #pragma unroll
   for (int r = 0; r < I::ROUNDS; ++r) {
@@ -484,26 +523,254 @@ __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int 
     bool xa;
     int ii, jj;
     if (it < I::NR && plane_item<TX, TY>(it, w, h, xa, ii, jj) && ii >= 0 && jj >= 0) {
-      T xl[NV], xr[NV], f[NV];
+      T xl[ND], xr[ND], f[ND];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
+      for (int v = 0; v < ND; ++v) {
         xr[v] = r < I::RREG ? QP[r < I::RREG ? r : 0][v] : S.QS[it - I::RREG * I::NTHR][v];
         xl[v] = xa ? S.FX[v][jj][ii] : S.FY[v][jj][ii];
       }
       T rr, pr;
+      bool left = false;
       if (xa) {
         xref(jj, rr, pr);
-        riemann_flux<T, NV, MIX, HLLC>(xl, xr, 1, rr, pr, gamma, inv_gm1, gm1, mx, f);
+        riemann_flux<T, ND, MIX, HLLC>(xl, xr, 1, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
       } else {
         sref(jj, rr, pr);
-        riemann_flux<T, NV, MIX, HLLC>(xl, xr, SNRM, rr, pr, gamma, inv_gm1, gm1, mx, f);
+        riemann_flux<T, ND, MIX, HLLC>(xl, xr, SNRM, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
       }
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
+      for (int v = 0; v < ND; ++v) {
         if (xa)
           S.FX[v][jj][ii] = f[v];
         else
           S.FY[v][jj][ii] = f[v];
+      }
+      if (ND < NV && r < I::RREG) {
+        T* dst = xa ? &S.FX[ND][jj][ii] : &S.FY[ND][jj][ii];
+        const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
+        const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
+                                 left);
+#pragma unroll
+        for (int v = ND; v < NV; ++v) {
+          dst[(v - ND) * dv] = f[0] * u.face(v * (TY + 6) * (TX + 6), eps, linear);
+          SNAP_VAR_FENCE();
+        }
+      }
+    }
+  }
+}
+
+// The tracer fluxes of the faces beyond the RREG rounds (64 of the 544 of a
+// 16 x 16 tile), one (face, tracer) pair per thread and pass so that every wave
+// takes a share (a barrier after phase_lmars; the upwind side is the mass
+// flux's sign).
+template <typename T, int NV, int ND, int TX, int TY>
+__device__ __forceinline__ void phase_tracer_rest(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
+                                                  bool linear) {
+  using I = PlaneItems<TX, TY>;
+  constexpr int NSP = I::NR - I::RREG * I::NTHR;
+  if constexpr (ND < NV && NSP > 0) {
+    constexpr int NSUB = NSP * (NV - ND);
+    const int t0 = item_thread<I::NTHR>();
+#pragma unroll
+    for (int m = 0; m < (NSUB + I::NTHR - 1) / I::NTHR; ++m) {
+      const int sub = t0 + m * I::NTHR;
+      const int v = ND + sub / NSP;
+      bool xa;
+      int ii, jj;
+      if (sub < NSUB &&
+          plane_item<TX, TY>(I::RREG * I::NTHR + sub % NSP, w, h, xa, ii, jj) && ii >= 0 &&
+          jj >= 0) {
+        const T f0 = xa ? S.FX[0][jj][ii] : S.FY[0][jj][ii];
+        const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
+                                 f0 > T(0));
+        const T q = u.face(v * (TY + 6) * (TX + 6), eps, linear);
+        (xa ? S.FX[v][jj][ii] : S.FY[v][jj][ii]) = f0 * q;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same phases for square tiles with the items' addresses packed, for the
+// 3-D kernels whose registers decide how many waves a SIMD holds. The addresses
+// of an item follow from its thread alone, so the compiler forms them before
+// the level loop and keeps every one (plane and face offsets per round and
+// phase) in a register of its own: 16 to 20 of them. Here an item is one word
+// per round, unpacked on every level (ItemCodes::get hides it from the
+// compiler's hoisting), and x and second-axis faces share one variable stride
+// (TX == TY), so that one offset serves both.
+// On 256 x 192 x 96 a double-precision step with two tracers then fits two waves
+// per SIMD: 1980 -> 1376 us; without tracers, where no wave is won, unpacking
+// costs 3.5 % (567 -> 585 us, single precision), so those kernels keep the
+// unpacked phases.
+// ---------------------------------------------------------------------------
+template <int NV, int TX, int TY>
+struct ItemCodes {
+  using I = PlaneItems<TX, TY>;
+  static constexpr int NSP = I::NR - I::RREG * I::NTHR;   // items beyond the rounds
+  static constexpr int PV = (TY + 6) * (TX + 6), DV = TY * (TX + 1), ROW = TX + 6;
+  static_assert(TX == TY && NSP > 0 && I::NTHR % NSP == 0 && PV <= 1024 && (NV + 1) * DV <= 4096,
+                "square tiles");
+  enum : unsigned { XA = 1u << 22, PUT = 1u << 23, VALID = 1u << 24, FACE = 1u << 25 };
+  unsigned c[I::RREG + 1];   // the rounds' items, then the item beyond them (by thread % NSP)
+
+  __device__ __forceinline__ ItemCodes(int w, int h) {
+    const int t0 = item_thread<I::NTHR>();
+#pragma unroll
+    for (int r = 0; r <= I::RREG; ++r) {
+      bool xa;
+      int ii, jj;
+      const bool ok = plane_item<TX, TY>(r * I::NTHR + (r < I::RREG ? t0 : t0 % NSP), w, h, xa, ii, jj);
+      const int src = xa ? (jj + 3) * ROW + ii + 1 : (jj + 1) * ROW + ii + 3;
+      const int dst = xa ? jj * (TX + 1) + ii + 1 : NV * DV + (jj + 1) * TX + ii;
+      c[r] = !ok ? 0u
+                 : (unsigned)src | (unsigned)dst << 10 | (xa ? XA : 0u) | VALID |
+                       ((xa ? ii < w : jj < h) ? PUT : 0u) | (ii >= 0 && jj >= 0 ? FACE : 0u);
+    }
+  }
+  __device__ __forceinline__ unsigned get(int r) const {
+    unsigned x = c[r];
+    asm volatile("" : "+v"(x));
+    return x;
+  }
+  // offsets of an item: its stencil (cell c-2) in the plane, the face c+1, the
+  // distance of two cells and of two faces of its line
+  static __device__ __forceinline__ int src(unsigned x) { return (int)(x & 1023u); }
+  static __device__ __forceinline__ int dst(unsigned x) { return (int)((x >> 10) & 4095u); }
+  static __device__ __forceinline__ int cell(unsigned x) { return (x & XA) ? 1 : ROW; }
+  static __device__ __forceinline__ int face(unsigned x) { return (x & XA) ? 1 : TX; }
+};
+
+// Phase R (as phase_reconstruct with SPLIT).
+template <typename T, int NV, int ND, int TX, int TY>
+__device__ __forceinline__ void packed_reconstruct(Plane<T, NV, TX, TY>& S,
+                                                   const ItemCodes<NV, TX, TY>& IC, T eps,
+                                                   bool linear,
+                                                   T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
+  using C = ItemCodes<NV, TX, TY>;
+  using I = PlaneItems<TX, TY>;
+  constexpr bool RPF = reconstruct_prefetch<T, NV>();
+  T* base = &S.P[0][0][0];
+  T* fb = reinterpret_cast<T*>(reinterpret_cast<char*>(&S) + sizeof(S.P));
+  constexpr int NSUB = C::NSP * ND;
+  {
+    const unsigned x = IC.get(I::RREG);
+    const int t0 = item_thread<I::NTHR>(), c = t0 % C::NSP, st = C::cell(x);
+#pragma unroll
+    for (int m = 0; m < (NSUB + I::NTHR - 1) / I::NTHR; ++m) {
+      const int sub = t0 + m * I::NTHR, v = sub / C::NSP;
+      if (sub < NSUB && (x & C::VALID)) {
+        const T* src = base + C::src(x) + v * C::PV;
+        T qm, qp;
+        weno5_cell<T>(src[0], src[st], src[2 * st], src[3 * st], src[4 * st], eps, linear, qm, qp);
+        if (x & C::PUT) fb[C::dst(x) + v * C::DV] = qm;
+        S.QS[c][v] = qp;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < I::RREG; ++r) {
+    const unsigned x = IC.get(r);
+    if (x & C::VALID) {
+      const int st = C::cell(x);
+      const T* src = base + C::src(x);
+      T* dst = fb + C::dst(x);
+      const bool put = (x & C::PUT) != 0;
+      T cur[5];
+      if constexpr (RPF) {
+#pragma unroll
+        for (int m = 0; m < 5; ++m) cur[m] = src[m * st];
+      }
+#pragma unroll
+      for (int v = 0; v < ND; ++v) {
+        T nxt[5];
+        if constexpr (RPF) {
+          if (v + 1 < ND) {
+#pragma unroll
+            for (int m = 0; m < 5; ++m) nxt[m] = src[(v + 1) * C::PV + m * st];
+          }
+        } else {
+#pragma unroll
+          for (int m = 0; m < 5; ++m) cur[m] = src[v * C::PV + m * st];
+        }
+        T qm;
+        weno5_cell<T>(cur[0], cur[1], cur[2], cur[3], cur[4], eps, linear, qm, QP[r][v]);
+        if (put) dst[v * C::DV] = qm;
+        SNAP_VAR_FENCE();
+        if constexpr (RPF) {
+          if (v + 1 < ND) {
+#pragma unroll
+            for (int m = 0; m < 5; ++m) cur[m] = nxt[m];
+          }
+        }
+      }
+    }
+  }
+}
+
+// Phase L (as phase_lmars; one reference rref, pref for every face of the level).
+template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool MIX, bool HLLC>
+__device__ __forceinline__ void packed_lmars(Plane<T, NV, TX, TY>& S,
+                                             const ItemCodes<NV, TX, TY>& IC, T eps, bool linear,
+                                             T gamma, T inv_gm1, T gm1, const Mixture& mx, T rref,
+                                             T pref, const T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
+  using C = ItemCodes<NV, TX, TY>;
+  using I = PlaneItems<TX, TY>;
+  T* base = &S.P[0][0][0];
+  T* fb = reinterpret_cast<T*>(reinterpret_cast<char*>(&S) + sizeof(S.P));
+#pragma unroll
+  for (int r = 0; r <= I::RREG; ++r) {
+    const unsigned x = IC.get(r);
+    if ((x & C::FACE) && (r < I::RREG || item_thread<I::NTHR>() < C::NSP)) {
+      T* fp = fb + C::dst(x) - C::face(x);
+      T xl[ND], xr[ND], f[ND];
+#pragma unroll
+      for (int v = 0; v < ND; ++v) {
+        xr[v] = r < I::RREG ? QP[r < I::RREG ? r : 0][v] : S.QS[item_thread<I::NTHR>()][v];
+        xl[v] = fp[v * C::DV];
+      }
+      bool left = false;
+      if (x & C::XA)
+        riemann_flux<T, ND, MIX, HLLC>(xl, xr, 1, rref, pref, gamma, inv_gm1, gm1, mx, f, left);
+      else
+        riemann_flux<T, ND, MIX, HLLC>(xl, xr, SNRM, rref, pref, gamma, inv_gm1, gm1, mx, f, left);
+#pragma unroll
+      for (int v = 0; v < ND; ++v) fp[v * C::DV] = f[v];
+      if (ND < NV && r < I::RREG) {
+        const int st = C::cell(x);
+        const UpwindStencil<T> u(base + C::src(x) - st, st, left);
+#pragma unroll
+        for (int v = ND; v < NV; ++v) {
+          fp[v * C::DV] = f[0] * u.face(v * C::PV, eps, linear);
+          SNAP_VAR_FENCE();
+        }
+      }
+    }
+  }
+}
+
+// As phase_tracer_rest.
+template <typename T, int NV, int ND, int TX, int TY>
+__device__ __forceinline__ void packed_tracer_rest(Plane<T, NV, TX, TY>& S,
+                                                   const ItemCodes<NV, TX, TY>& IC, T eps,
+                                                   bool linear) {
+  using C = ItemCodes<NV, TX, TY>;
+  using I = PlaneItems<TX, TY>;
+  if constexpr (ND < NV) {
+    constexpr int NSUB = C::NSP * (NV - ND);
+    T* base = &S.P[0][0][0];
+    T* fb = reinterpret_cast<T*>(reinterpret_cast<char*>(&S) + sizeof(S.P));
+    const unsigned x = IC.get(I::RREG);
+    if (x & C::FACE) {
+      T* fp = fb + C::dst(x) - C::face(x);
+      const T f0 = fp[0];
+      const int st = C::cell(x);
+      const UpwindStencil<T> u(base + C::src(x) - st, st, f0 > T(0));
+#pragma unroll
+      for (int m = 0; m < (NSUB + I::NTHR - 1) / I::NTHR; ++m) {
+        const int sub = item_thread<I::NTHR>() + m * I::NTHR, v = ND + sub / C::NSP;
+        if (sub < NSUB) fp[v * C::DV] = f0 * u.face(v * C::PV, eps, linear);
       }
     }
   }
@@ -527,9 +794,9 @@ __device__ __forceinline__ bool halo_item(int it, int w, int h, int& ii, int& jj
 }
 
 // The 3-D kernels that split the reconstruction's last items by variable
-// (phase_reconstruct): not those with the sedimentation terms, which are held
-// to two waves per SIMD in single precision (with six tracers the split took
-// the spilled registers from 3 to 11).
+// (phase_reconstruct; the packed form always does): not the unpacked ones with
+// the sedimentation terms, which are held to two waves per SIMD in single
+// precision.
 template <typename T, int NT, bool MIX, bool SED>
 constexpr bool split_reconstruct() {
   return !SED;
@@ -538,10 +805,6 @@ constexpr bool split_reconstruct() {
 // ---------------------------------------------------------------------------
 // 3-D kernel
 // ---------------------------------------------------------------------------
-#ifndef SNAP_STAGE3D_WAVES_PER_EU
-#define SNAP_STAGE3D_WAVES_PER_EU 1
-#endif
-
 template <typename T, int NV>
 __device__ __forceinline__ void load_cons(const T* __restrict__ q, long long off, long long sv,
                                           T (&c)[NV]) {
@@ -569,22 +832,47 @@ __device__ __forceinline__ void cons_to_prim_t(const T (&c)[NV], const LevelRef&
 // frictional heating, sediment_cell) are added to the right-hand side in phase
 // D from the window's levels s-1, s, s+1; these instances load nothing a
 // level ahead, which makes room for that work in the registers.
-// The sedimentation instances in single precision are held to two waves per
-// SIMD, and so are the single-precision mixture with six or seven tracers and
-// the double-precision sedimentation instance with one tracer (unheld they
-// take 258 to 262 registers); the other kernels with up to eight tracers in
-// single precision and one in double precision reach it unaided.
-template <typename T, int NT, bool MIX, bool SED>
-constexpr int stage3d_min_waves() {
-  if constexpr (sizeof(T) == 4)
-    return (SED || (MIX && (NT == 6 || NT == 7))) ? 2 : SNAP_STAGE3D_WAVES_PER_EU;
-  else
-    return (SED && NT == 1) ? 2 : SNAP_STAGE3D_WAVES_PER_EU;
-}
-
+//
+// Registers decide how many waves a SIMD holds (168 each for three, 256 for
+// two), and the kernels with tracers sit around those steps. Per instance:
+//   pack   item addresses packed (ItemCodes): 16 to 20 registers fewer for 3.5 %
+//          more instructions, where that saves a wave or the spills;
+//   ahead  the next level's halo, window and stage-combination values loaded a
+//          level ahead: 4 NV registers, where they leave the waves in place;
+//   waves  the waves per SIMD the registers are held to (1: left alone).
+// Microseconds per SSP-RK3 step on 256 x 192 x 96 with passive tracers, before
+// (every variable two-sided, unpacked, loaded ahead in single precision) and now:
+//   single precision   2 tracers 918, 756; 3: 1027, 861; 4: 1145, 953; 5: 1241, 1095
+//   double precision   2 tracers 1983, 1370; 3: 2237, 1722; 4 (HLLC): 2614, 2251
+// Packed further, single precision with six tracers took 1345 -> 1390 us (72 bytes
+// of scratch per lane), so from six on the registers are left alone. The
+// sedimentation instances load nothing ahead, which makes room for their fall
+// fluxes, and are held to two waves; packed from six tracers on, where they
+// spilled (moist step with six tracers on 160 x 144 x 96: 1020 -> 961 us).
+// LOW: a launch of at most one workgroup per compute unit, which more waves per
+// SIMD do not help: the instances whose held registers spill leave them alone
+// there (75 x 60 x 40, double precision, 3 tracers: 187 held, 175 us).
+template <typename T, int NT, bool MIX, bool SED, bool LOW = false>
+struct Stage3DShape {
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr bool pack = SED   ? F32 && NT >= 6
+                               : MIX ? F32 && (NT == 6 || NT == 8)
+                               : F32 ? NT == 4 || (NT == 5 && !LOW)
+                                     : NT >= 2 && NT <= 4;
+  static constexpr bool ahead =
+      !SED && (F32 ? NT <= 6 && (MIX || NT == 0 || NT == 6 || LOW) : NT == 0);
+  static constexpr int waves = LOW                    ? 1
+                               : SED                  ? (F32 || NT == 1 ? 2 : 1)
+                               : MIX                  ? (F32 && NT >= 6 ? 2 : 1)
+                               : F32 && NT >= 1 && NT <= 5 ? 3
+                               : !F32 && NT >= 2 && NT <= 4 ? 2
+                                                      : 1;
+  // the held instances that spill, for which a LOW one exists
+  static constexpr bool has_low = !MIX && !SED && (F32 ? NT == 5 : NT == 3 || NT == 4);
+};
 template <typename T, int NT, int TX, int TY, bool MIX = false, bool HLLC = false,
-          bool SED = false>
-__global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>()))
+          bool SED = false, bool LOW = false>
+__global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::waves))
     k_stage3d(StageArgs a) {
   constexpr int NV = 5 + NT;
   constexpr bool GF = ghosts_in_place(NT);
@@ -592,11 +880,7 @@ __global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>())
   using I = PlaneItems<TX, TY>;
   constexpr int NHALO = 6 * (TX + TY);
   constexpr int HR = (NHALO + I::NTHR - 1) / I::NTHR;   // halo items per thread
-  // Load the next level's halo, window and stage-combination values a level
-  // ahead only where the extra 4 NV live values still leave room for two
-  // waves per SIMD (256 registers); with more variables each value is loaded
-  // where it is used.
-  constexpr bool PF = !SED && (sizeof(T) == 4 ? NV <= 11 : NV <= 5);
+  constexpr bool PF = Stage3DShape<T, NT, MIX, SED, LOW>::ahead;
   __shared__ Plane<T, NV, TX, TY> S;
   const T* __restrict__ qs = static_cast<const T*>(a.qs);
 
@@ -684,8 +968,11 @@ __global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>())
     return k;
   };
 
+  constexpr int ND = two_sided<T, NV, MIX, true>();
   T W[5][NV];     // primitives of levels s-1 .. s+3 (own column)
-  T qmc[NV];      // left state at the vertical face above the current level
+  // left states at the vertical face above the current level; for the tracers
+  // that are reconstructed on the upwind side only, their values on level s-2
+  T qmc[NV];
   T fzc[NV];      // vertical flux at the lower face of the current level
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
@@ -722,7 +1009,9 @@ __global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>())
     }
   };
 
-  T QP[I::RREG][NV];
+  T QP[I::RREG][ND];
+  constexpr bool PACK = Stage3DShape<T, NT, MIX, SED, LOW>::pack;
+  const ItemCodes<PACK ? NV : 1, PACK ? TX : 16, PACK ? TY : 16> IC(w, h);
   for (int s = k0 - 2; s < k1; ++s) {
     T wc[NV], qsc[NV], qnc[NV];
     bool wzf;
@@ -761,8 +1050,11 @@ __global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>())
       }
       __syncthreads();
       // ---- (R) WENO5 in x and y ---------------------------------------------
-      phase_reconstruct<T, NV, TX, TY, split_reconstruct<T, NT, MIX, SED>()>(S, w, h, eps,
-                                                                            linear, QP);
+      if constexpr (PACK)
+        packed_reconstruct<T, NV, ND, TX, TY>(S, IC, eps, linear, QP);
+      else
+        phase_reconstruct<T, NV, ND, TX, TY, split_reconstruct<T, NT, MIX, SED>()>(S, w, h, eps,
+                                                                                  linear, QP);
       __syncthreads();
       // ---- (L) LMARS at x and y faces (level references) ---------------------
       const T rbT = static_cast<T>(rbs), pbT = static_cast<T>(pbs);
@@ -770,9 +1062,17 @@ __global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>())
         r = rbT;
         p = pbT;
       };
-      phase_lmars<T, NV, TX, TY, 2, MIX, HLLC>(S, w, h, gamma, inv_gm1, gm1t, a.mix, levref,
-                                            levref, QP);
-      __syncthreads();
+      if constexpr (PACK) {
+        packed_lmars<T, NV, ND, TX, TY, 2, MIX, HLLC>(S, IC, eps, linear, gamma, inv_gm1, gm1t,
+                                                      a.mix, rbT, pbT, QP);
+        __syncthreads();
+        packed_tracer_rest<T, NV, ND, TX, TY>(S, IC, eps, linear);
+      } else {
+        phase_lmars<T, NV, ND, TX, TY, 2, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t,
+                                                     a.mix, levref, levref, QP);
+        __syncthreads();
+        phase_tracer_rest<T, NV, ND, TX, TY>(S, w, h, eps, linear);
+      }
     }
     // ---- vertical direction, own column: face s+1/2 (z-face index s+1) -------
     T dfz[NV];
@@ -781,27 +1081,45 @@ __global__ void __launch_bounds__(TX* TY, (stage3d_min_waves<T, NT, MIX, SED>())
       if (wzf) wc[3] = -wc[3];
       cons_to_prim_t<T, NV, MIX>(wc, level_ref(a.pert, a.rbar_c[s + 3 + NG], a.pbar_c[s + 3 + NG]),
                                  a.gm1, a.mix, W[4]);
-      T qmn[NV], qpn[NV];
+      T qmn[ND], qpn[ND];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
+      for (int v = 0; v < ND; ++v) {
         weno5_cell<T>(W[0][v], W[1][v], W[2][v], W[3][v], W[4][v], eps, linear, qmn[v], qpn[v]);
         SNAP_VAR_FENCE();
       }
       if (s >= k0 - 1) {
-        T fz[NV];
-        riemann_flux<T, NV, MIX, HLLC>(qmc, qpn, 3, static_cast<T>(a.rbar_f[s + 1]),
-                                       static_cast<T>(a.pbar_f[s + 1]), gamma, inv_gm1, gm1t,
-                                       a.mix, fz);
+        T fz[ND];
+        bool left = false;
+        T xl[ND];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
+        for (int v = 0; v < ND; ++v) xl[v] = qmc[v];
+        riemann_flux<T, ND, MIX, HLLC>(xl, qpn, 3, static_cast<T>(a.rbar_f[s + 1]),
+                                       static_cast<T>(a.pbar_f[s + 1]), gamma, inv_gm1, gm1t,
+                                       a.mix, fz, left);
+#pragma unroll
+        for (int v = 0; v < ND; ++v) {
           dfz[v] = fz[v] - fzc[v];
           fzc[v] = fz[v];
         }
+        // tracers: the upwind side's value (levels s-2 .. s+2 up, or s+3 .. s-1 down)
+#pragma unroll
+        for (int v = ND; v < NV; ++v) {
+          const T q = weno5_face<T>(left ? qmc[v] : W[4][v], left ? W[0][v] : W[3][v],
+                                    left ? W[1][v] : W[2][v], left ? W[2][v] : W[1][v],
+                                    left ? W[3][v] : W[0][v], eps, linear);
+          const T fq = fz[0] * q;
+          dfz[v] = fq - fzc[v];
+          fzc[v] = fq;
+          SNAP_VAR_FENCE();
+        }
       }
 #pragma unroll
-      for (int v = 0; v < NV; ++v) qmc[v] = qmn[v];
+      for (int v = 0; v < ND; ++v) qmc[v] = qmn[v];
+#pragma unroll
+      for (int v = ND; v < NV; ++v) qmc[v] = W[0][v];
     }
     // ---- (D) divergence, gravity, output -------------------------------------
+    if (ND < NV && s >= k0) __syncthreads();   // the last tracer fluxes
     if (s >= k0 && act) {
       if constexpr (!PF) load_own(s, qsc, qnc);
       T R[NV];
@@ -945,8 +1263,9 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
     }
   }
   __syncthreads();
-  T QP[I::RREG][NV];
-  phase_reconstruct<T, NV, TX, TZ>(S, w, h, eps, linear, QP);
+  constexpr int ND = two_sided<T, NV, MIX, false>();
+  T QP[I::RREG][ND];
+  phase_reconstruct<T, NV, ND, TX, TZ>(S, w, h, eps, linear, QP);
   __syncthreads();
   auto xref = [&](int kk, T& r, T& p) {
     r = static_cast<T>(a.rbar_c[k0 + kk + NG]);
@@ -956,8 +1275,13 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
     r = static_cast<T>(a.rbar_f[k0 + fk]);
     p = static_cast<T>(a.pbar_f[k0 + fk]);
   };
-  phase_lmars<T, NV, TX, TZ, 3, MIX, HLLC>(S, w, h, gamma, inv_gm1, gm1t, a.mix, xref, zref, QP);
+  phase_lmars<T, NV, ND, TX, TZ, 3, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t, a.mix,
+                                               xref, zref, QP);
   __syncthreads();
+  if constexpr (ND < NV) {
+    phase_tracer_rest<T, NV, ND, TX, TZ>(S, w, h, eps, linear);
+    __syncthreads();
+  }
   unsigned long long smx = 0ULL;
   if (act) {
     T R[NV];
