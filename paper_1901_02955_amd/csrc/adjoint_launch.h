@@ -8,33 +8,46 @@
 
 namespace snap {
 
-template <typename T, int NV, bool XDIR, bool HLLC, bool MIX>
-void adj_line_launch(const T* q, const T* r, const AdjArgs& a, int d, T* P, hipStream_t st) {
-  constexpr int LN = LineShape<T, NV, XDIR>::LN, TL = LineShape<T, NV, XDIR>::TL;
-  const LineGeom g = line_geom(a, d);
-  const long long blocks = ((g.nlines + LN - 1) / LN) * ((g.nd + TL - 1) / TL);
-  hipLaunchKernelGGL((k_adj_line<T, NV, LN, TL, XDIR, HLLC, MIX>), dim3((unsigned)blocks),
-                     dim3(LineTile<T, NV, LN, TL>::NTHR), 0,
-                     st, q, r, a, d, P);
+template <typename T, int NV, int D, bool HLLC, bool MIX>
+void adj_lane_launch(const T* q, const T* r, const AdjArgs& a, T* P, const FoldOut<T>& fo,
+                     hipStream_t st) {
+  constexpr int NW = lane_waves<T, D>();
+  const int nseg = lane_segments(D == 0 ? a.nx : (D == 1 ? a.ny : a.nz));
+  const long long groups = D == 0 ? ((long long)a.ny * a.nz + NW - 1) / NW
+                                  : (long long)((a.nx + NW - 1) / NW) * (D == 1 ? a.nz : a.ny);
+  hipLaunchKernelGGL((k_adj_lane<T, NV, D, HLLC, MIX>), dim3((unsigned)(groups * nseg)),
+                     dim3(64 * NW), 0, st, q, r, a, nseg, P, fo);
 }
 
 // The y and z directions march along their lines (k_adj_march) in single
 // precision with up to 7 variables, where the march's register window fits,
-// and where each variable's padded plane is smaller than 2 GiB; double
-// precision, more variables and larger planes take the tiled kernel. Setting
-// SNAP_ADJ_MARCH=0 selects the tiled kernel everywhere.
+// where each variable's padded plane is smaller than 2 GiB, and on grids where
+// it is the faster one (march_pays); otherwise they take the lane kernel. In
+// double precision the march's window needs over 256 registers (five variables:
+// 240 bytes of scratch per lane at two waves per SIMD). SNAP_ADJ_MARCH=0 selects
+// the lane kernel everywhere, SNAP_ADJ_MARCH=1 (or a segment length in
+// SNAP_ADJ_MARCH_SEG) the march on every grid where it fits.
 template <typename T, int NV>
 constexpr bool march_fits() {
   return sizeof(T) == 4 && NV <= 7;
 }
 
+// The march holds more cells per instruction (no halo lanes) but needs long
+// lines in large numbers to fill the chip; the lane kernel fills it on any
+// grid. Microseconds of one gradient step (single precision; march, lane):
+// 5 variables 96x96x48 486, 376; 160x160x80 1247, 1172; 192x160x96 (six steps)
+// 6881, 6652; 256x256x128 4002, 4580;
+// 7 variables 96x96x48 637, 489; 160x160x80 1674, 1612; 256x256x128 5850, 6575.
 // (read at every launch, so that a process can compare both kernels)
-inline bool march_enabled() {
+inline bool march_pays(const AdjArgs& a) {
   const char* e = getenv("SNAP_ADJ_MARCH");
-  return !(e && e[0] == '0');
+  if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
+  const char* seg = getenv("SNAP_ADJ_MARCH_SEG");
+  if (seg && atoi(seg) > 0) return true;
+  return (double)a.nx * a.ny * a.nz >= 4.2e6;
 }
 
-// The z march folds the cells at least 3 from the y and z edges, after
+// The z direction folds the cells at least 3 from the y and z edges, after
 // k_adj_xmerge has added the x copies' cotangents into the cells within 3 of
 // an x edge (the separate fold pass then covers the rows of the 3 lowest and 3
 // highest levels and those within 3 of a y edge); SNAP_ADJ_MARCH_FOLD=0
@@ -44,18 +57,35 @@ inline bool march_fold_enabled() {
   return !(e && e[0] == '0');
 }
 
-// Segment length of the march: at most 43 cells, so that the 256 x 256 x 128
-// grid gives 3 x 65536 z segments and 6 x 32768 y segments (three waves per
-// SIMD of the 256 compute units, the kernel's occupancy with 5 variables),
-// each recomputing a 3-cell halo on either side. On that grid one FP32
-// right-hand-side adjoint took 1.100, 1.107, 1.085 and 1.133 ms with segments
-// of 24, 32, 43 and 64 cells. SNAP_ADJ_MARCH_SEG overrides the length.
-inline int march_seglen(int nd) {
+// Segment length of the march. A line is cut into as many segments as make the
+// launch fastest by this estimate: a segment takes its cells plus 6 for the halo
+// it recomputes; m = blocks per compute unit share each SIMD, which issues 0.5,
+// 0.8 or 0.95 of the time with one, two or three waves (up to `waves` at once).
+// For 256 x 256 x 128 that gives 43-cell z and y segments, the measured best
+// (24, 32, 43 and 64 cells: 1.100, 1.107, 1.085 and 1.133 ms per right-hand-side
+// adjoint); for 192 x 160 x 96, where 32-cell segments left one to two waves per
+// SIMD, 16 cells (189 -> 140 us in z, 176 -> 123 in y). SNAP_ADJ_MARCH_SEG
+// overrides the length.
+inline int march_seglen(int nd, long long lines, int waves) {
   const char* e = getenv("SNAP_ADJ_MARCH_SEG");
   const int v = e ? atoi(e) : 0;
-  const int target = v > 0 ? v : 43;
-  const int nseg = (nd + target - 1) / target;
-  return (nd + nseg - 1) / nseg;
+  int best = (nd + (v > 0 ? v : nd) - 1) / (v > 0 ? v : nd);
+  if (v <= 0) {
+    constexpr double issue[3] = {0.5, 0.8, 0.95};
+    constexpr long long CUS = 256;
+    const long long row = (lines + 255) / 256;
+    double cost = 1e300;
+    for (int n = 1; n <= nd / 4 + 1; ++n) {
+      const int len = (nd + n - 1) / n;
+      const long long m = (row * ((nd + len - 1) / len) + CUS - 1) / CUS;
+      const double c = (double)m * (len + 6) / issue[(m < waves ? m : waves) - 1];
+      if (c < cost) {
+        cost = c;
+        best = n;
+      }
+    }
+  }
+  return (nd + best - 1) / best;
 }
 
 template <typename T, int NV, int D, bool HLLC>
@@ -63,7 +93,7 @@ void adj_march_launch(const T* q, const T* r, const AdjArgs& a, T* P, const Marc
                       hipStream_t st) {
   const int nd = D == 2 ? a.nz : a.ny;
   const long long lines = (long long)a.nx * (D == 2 ? a.ny : a.nz);
-  const int seg = march_seglen(nd);
+  const int seg = march_seglen(nd, lines, NV <= 5 ? 3 : 2);
   const dim3 grid((unsigned)((lines + 255) / 256), (unsigned)((nd + seg - 1) / seg));
   hipLaunchKernelGGL((k_adj_march<T, NV, D, HLLC>), grid, dim3(256), 0, st, q, r, a, seg, P, fo);
 }
@@ -74,29 +104,37 @@ int adj_rhs_nv(const AdjWork& w, const AdjArgs& a, const void* q, const void* rb
   const T* qs = static_cast<const T*>(q);
   const T* r = static_cast<const T*>(rb);
   T* P = static_cast<T*>(w.P);
-  adj_line_launch<T, NV, true, HLLC, MIX>(qs, r, a, 0, P, st);
+  FoldOut<T> fo{static_cast<T*>(out), static_cast<const T*>(y), mode, 0, alpha, beta, gam};
+  adj_lane_launch<T, NV, 0, HLLC, MIX>(qs, r, a, P, fo, st);
   // the march addresses each variable's plane with 32-bit byte offsets
   const bool planes_small = a.sv * (long long)sizeof(T) < (1LL << 31) &&
                             a.rv * (long long)sizeof(T) < (1LL << 31);
-  // (the mixture takes the tiled kernel in every direction)
-  bool zfold = false;   // the z march folds the cells at least 3 from the y and z edges
-  if (march_fits<T, NV>() && !MIX && march_enabled() && planes_small) {
-    if constexpr (march_fits<T, NV>() && !MIX) {
-      zfold = march_fold_enabled() && a.nz > 6;
-      MarchFold<T> none{nullptr, nullptr, 0, T(0), T(0), T(0)};
-      MarchFold<T> fo{static_cast<T*>(out), static_cast<const T*>(y), mode,
-                      static_cast<T>(alpha), static_cast<T>(beta), static_cast<T>(gam)};
-      if (zfold) {
-        const long long n = (long long)(a.nx > 6 ? 6 : a.nx) * a.ny * a.nz;
-        hipLaunchKernelGGL((k_adj_xmerge<T, NV>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                           st, P, a);
-      }
+  // the z direction folds the cells at least 3 from the y and z edges (not
+  // under the mixture, whose fold costs the z kernel what it saves: 96 x 80 x 64
+  // with six tracers in double precision 174 us and 71 for the separate fold,
+  // against 219 and 19)
+  const bool zfold = march_fold_enabled() && a.nz > 6 && !MIX;
+  if (zfold) {
+    const long long n = (long long)(a.nx > 6 ? 6 : a.nx) * a.ny * a.nz;
+    hipLaunchKernelGGL((k_adj_xmerge<T, NV>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                       P, a);
+  }
+  bool marched = false;
+  if constexpr (march_fits<T, NV>() && !MIX) {
+    if (planes_small && march_pays(a)) {
+      const MarchFold<T> none{nullptr, nullptr, 0, T(0), T(0), T(0)};
+      const MarchFold<T> mf{static_cast<T*>(out), static_cast<const T*>(y), mode,
+                            static_cast<T>(alpha), static_cast<T>(beta), static_cast<T>(gam)};
       if (a.d3) adj_march_launch<T, NV, 1, HLLC>(qs, r, a, P, none, st);
-      adj_march_launch<T, NV, 2, HLLC>(qs, r, a, P, zfold ? fo : none, st);
+      adj_march_launch<T, NV, 2, HLLC>(qs, r, a, P, zfold ? mf : none, st);
+      marched = true;
     }
-  } else {
-    if (a.d3) adj_line_launch<T, NV, false, HLLC, MIX>(qs, r, a, 1, P, st);
-    adj_line_launch<T, NV, false, HLLC, MIX>(qs, r, a, 2, P, st);
+  }
+  if (!marched) {
+    if (a.d3) adj_lane_launch<T, NV, 1, HLLC, MIX>(qs, r, a, P, fo, st);
+    FoldOut<T> zf = fo;
+    zf.fold = zfold ? 1 : 0;
+    adj_lane_launch<T, NV, 2, HLLC, MIX>(qs, r, a, P, zf, st);
   }
   // falling condensates (mixture): the reverse of the sedimentation terms
   if constexpr (MIX) {
@@ -109,8 +147,7 @@ int adj_rhs_nv(const AdjWork& w, const AdjArgs& a, const void* q, const void* rb
   const int ye = !a.d3 ? 0 : (a.ny > 6 ? 6 : a.ny);
   const int rows = zfold ? 6 * a.ny + (a.nz - 6) * ye : a.ny * a.nz;
   const dim3 fgrid(rows, (a.nx + 255) / 256);
-  hipLaunchKernelGGL((k_adj_consfold<T, NV, MIX>), fgrid, dim3(256), 0, st, qs, P, r, a,
-                     static_cast<T*>(out), mode, alpha, beta, static_cast<const T*>(y), gam,
+  hipLaunchKernelGGL((k_adj_consfold<T, NV, MIX>), fgrid, dim3(256), 0, st, qs, P, r, a, fo,
                      zfold ? 1 : 0);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }

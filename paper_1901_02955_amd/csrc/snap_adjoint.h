@@ -5,21 +5,21 @@
 // ghost cells being functions of the interior through the boundary conditions.
 //
 // The reverse sweep uses no atomics, so the result is reproducible bit for bit:
-//   k_adj_line<d>    per direction d, per tile of lines: the primitives of
-//                    the tile's cells from the state (as in the forward
-//                    pass), the WENO face states recomputed, LMARS forward
-//                    and reverse with the flux cotangent
+//   k_adj_lane<d>    per direction d, with the cells of a line in the lanes of a
+//                    wave: the primitives from the state (as in the forward
+//                    pass), the WENO face states recomputed, the Riemann flux
+//                    forward and reverse with the flux cotangent
 //                    F_bar = (r_bar[right cell] - r_bar[left cell]) / dx_d,
-//                    the WENO5 reverse to the five stencil inputs, and a
-//                    fixed-order gather of those contributions into the
-//                    primitive cotangent;
-//   k_adj_march<d>   the same for the y and z directions in single precision,
-//                    one thread per line segment marching along it; the z
-//                    march also folds (below) the cells at least 3 from the
-//                    y and z edges, in single precision;
-//   k_adj_xmerge     before a folding z march: the x ghost cells' primitive
+//                    the WENO5 reverse to the five stencil inputs, and the
+//                    fixed-order sum of those contributions in the primitive
+//                    cotangent;
+//   k_adj_march<d>   the same for the y and z directions of large grids in
+//                    single precision, one thread per line segment marching
+//                    along it; the z direction of either also folds (below)
+//                    the cells at least 3 from the y and z edges;
+//   k_adj_xmerge     before a folding z direction: the x ghost cells' primitive
 //                    cotangents added into the cells they copy;
-//   k_adj_consfold   per interior cell (after a folding z march: the rest):
+//   k_adj_consfold   per interior cell (after a folding z direction: the rest):
 //                    gravity terms and the
 //                    reverse of the conserved -> primitive map (double
 //                    precision) for the cell and for each ghost cell that
@@ -52,166 +52,9 @@ struct AdjArgs {
   const double* pbar_f;
 };
 
-// Box of a per-direction work array: interior sizes with `ext` extra points
-// along direction d (faces: 1, reconstructed cells: 2).
-struct DirBox {
-  int n[3];   // extents along x, y, z
-  long long total;
-};
-
-__host__ __device__ inline DirBox dir_box(const AdjArgs& a, int d, int ext) {
-  DirBox b;
-  b.n[0] = a.nx + (d == 0 ? ext : 0);
-  b.n[1] = a.ny + (d == 1 ? ext : 0);
-  b.n[2] = a.nz + (d == 2 ? ext : 0);
-  b.total = (long long)b.n[0] * b.n[1] * b.n[2];
-  return b;
-}
-
-__device__ __forceinline__ void box_coords(const DirBox& b, long long g, int& x, int& y, int& z) {
-  x = (int)(g % b.n[0]);
-  const long long r = g / b.n[0];
-  y = (int)(r % b.n[1]);
-  z = (int)(r / b.n[1]);
-}
-
-__device__ __forceinline__ long long box_index(const DirBox& b, int x, int y, int z) {
-  return ((long long)z * b.n[1] + y) * b.n[0] + x;
-}
-
 // padded offset of interior coordinates (i, j, k) (ghosts allowed)
 __device__ __forceinline__ long long padded_off(const AdjArgs& a, int i, int j, int k) {
   return (long long)(k + NG) * a.sz + (long long)(j + a.gy) * a.sy + (i + NG);
-}
-
-// ---------------------------------------------------------------------------
-// WENO5 of one cell split for the reverse sweep (same formulation as
-// weno5_cell). weno5_lin returns both face values and keeps the forward
-// quantities the linearisation needs; weno5_rev maps the cotangents gm of qm
-// and gp of qp back to the five inputs a..e.
-// As in weno5_cell the smoothness sums are formed as 4 s_k = 4 eps + (13/3)
-// u_k^2 + v_k^2 (the normalised weights depend only on their ratios), and
-// they are scaled by a common power of two (exact) so that the products of
-// squared sums below stay in range in single precision.
-// ---------------------------------------------------------------------------
-template <typename T>
-struct WenoLin {
-  T s0, s1, s2, sc;                // scaled smoothness sums, and the scale
-  T wm0, wm1, wm2, wp0, wp1, wp2;  // normalised weights of qm and of qp
-  T idm, idp;                      // reciprocals of the unnormalised weight sums
-};
-
-template <typename T>
-__device__ __forceinline__ void weno5_lin(T a, T b, T c, T d, T e, T eps, bool linear,
-                                          WenoLin<T>& L, T& qm, T& qp) {
-  const T da = a - c, db = b - c, dd = d - c, de = e - c;
-  const T m0 = T(2) * da - T(7) * db, m1 = T(2) * dd - db, m2 = T(5) * dd - de;
-  const T p0 = T(2) * de - T(7) * dd, p1 = T(2) * db - dd, p2 = T(5) * db - da;
-  const T sixth = T(1) / T(6);
-  if (linear) {
-    qm = c + (T(0.1) * m0 + T(0.6) * m1 + T(0.3) * m2) * sixth;
-    qp = c + (T(0.1) * p0 + T(0.6) * p1 + T(0.3) * p2) * sixth;
-    return;
-  }
-  const T k13 = T(13) / T(3), eps4 = T(4) * eps;
-  const T u0 = fma(T(-2), db, da), v0 = fma(T(-4), db, da);
-  const T u1 = db + dd, v1 = db - dd;
-  const T u2 = fma(T(-2), dd, de), v2 = fma(T(-4), dd, de);
-  T s0 = fma(v0, v0, fma(k13 * u0, u0, eps4));
-  T s1 = fma(v1, v1, fma(k13 * u1, u1, eps4));
-  T s2 = fma(v2, v2, fma(k13 * u2, u2, eps4));
-  T sc;
-  if constexpr (sizeof(T) == 4) {
-    const float mx = fmaxf(fmaxf(s0, s1), s2);
-    sc = __builtin_amdgcn_ldexpf(1.0f, -__builtin_amdgcn_frexp_expf(mx));
-  } else {
-    const double mx = fmax(fmax(s0, s1), s2);
-    sc = __builtin_amdgcn_ldexp(1.0, -__builtin_amdgcn_frexp_exp(mx));
-  }
-  s0 *= sc;
-  s1 *= sc;
-  s2 *= sc;
-  const T q0 = s0 * s0, q1 = s1 * s1, q2 = s2 * s2;
-  const T t0 = q1 * q2, t1 = q0 * q2, t2 = q0 * q1;
-  const T n0 = T(0.1) * t0, n1 = T(0.6) * t1, n2 = T(0.3) * t2;
-  const T r0 = T(0.1) * t2, r1 = T(0.6) * t1, r2 = T(0.3) * t0;
-  const T idm = rcp_fast(n0 + n1 + n2), idp = rcp_fast(r0 + r1 + r2);
-  L.s0 = s0;
-  L.s1 = s1;
-  L.s2 = s2;
-  L.sc = sc;
-  L.wm0 = n0 * idm;
-  L.wm1 = n1 * idm;
-  L.wm2 = n2 * idm;
-  L.wp0 = r0 * idp;
-  L.wp1 = r1 * idp;
-  L.wp2 = r2 * idp;
-  L.idm = idm;
-  L.idp = idp;
-  qm = c + (L.wm0 * m0 + L.wm1 * m1 + L.wm2 * m2) * sixth;
-  qp = c + (L.wp0 * p0 + L.wp1 * p1 + L.wp2 * p2) * sixth;
-}
-
-template <typename T>
-__device__ __forceinline__ void weno5_rev(T a, T b, T c, T d, T e, bool linear,
-                                          const WenoLin<T>& L, T gm, T gp, T (&g)[5]) {
-  const T da = a - c, db = b - c, dd = d - c, de = e - c;
-  const T sixth = T(1) / T(6);
-  T mb0, mb1, mb2, pb0, pb1, pb2;
-  T ub0 = T(0), vb0 = T(0), ub1 = T(0), vb1 = T(0), ub2 = T(0), vb2 = T(0);
-  if (linear) {
-    mb0 = gm * T(0.1) * sixth;
-    mb1 = gm * T(0.6) * sixth;
-    mb2 = gm * T(0.3) * sixth;
-    pb0 = gp * T(0.1) * sixth;
-    pb1 = gp * T(0.6) * sixth;
-    pb2 = gp * T(0.3) * sixth;
-  } else {
-    const T m0 = T(2) * da - T(7) * db, m1 = T(2) * dd - db, m2 = T(5) * dd - de;
-    const T p0 = T(2) * de - T(7) * dd, p1 = T(2) * db - dd, p2 = T(5) * db - da;
-    const T Mm = L.wm0 * m0 + L.wm1 * m1 + L.wm2 * m2;   // 6 (qm - c)
-    const T Mp = L.wp0 * p0 + L.wp1 * p1 + L.wp2 * p2;
-    const T gms = gm * sixth, gps = gp * sixth;
-    mb0 = gms * L.wm0;
-    mb1 = gms * L.wm1;
-    mb2 = gms * L.wm2;
-    pb0 = gps * L.wp0;
-    pb1 = gps * L.wp1;
-    pb2 = gps * L.wp2;
-    // cotangents of the unnormalised weights
-    const T gmD = gms * L.idm, gpD = gps * L.idp;
-    const T nb0 = gmD * (m0 - Mm), nb1 = gmD * (m1 - Mm), nb2 = gmD * (m2 - Mm);
-    const T rb0 = gpD * (p0 - Mp), rb1 = gpD * (p1 - Mp), rb2 = gpD * (p2 - Mp);
-    const T tb0 = T(0.1) * nb0 + T(0.3) * rb2;
-    const T tb1 = T(0.6) * (nb1 + rb1);
-    const T tb2 = T(0.3) * nb2 + T(0.1) * rb0;
-    const T q0 = L.s0 * L.s0, q1 = L.s1 * L.s1, q2 = L.s2 * L.s2;
-    const T qb0 = tb1 * q2 + tb2 * q1;
-    const T qb1 = tb0 * q2 + tb2 * q0;
-    const T qb2 = tb0 * q1 + tb1 * q0;
-    // cotangent of the unscaled 4 s_k: sc * 2 s'_k * qb_k (s'_k the scaled
-    // sum kept by the forward), times d(4 s)/du = (26/3) u and d(4 s)/dv = 2 v
-    const T two_sc = T(2) * L.sc;
-    const T bb0 = two_sc * L.s0 * qb0;
-    const T bb1 = two_sc * L.s1 * qb1;
-    const T bb2 = two_sc * L.s2 * qb2;
-    const T k263 = T(26) / T(3);
-    ub0 = k263 * fma(T(-2), db, da) * bb0;
-    vb0 = T(2) * fma(T(-4), db, da) * bb0;
-    ub1 = k263 * (db + dd) * bb1;
-    vb1 = T(2) * (db - dd) * bb1;
-    ub2 = k263 * fma(T(-2), dd, de) * bb2;
-    vb2 = T(2) * fma(T(-4), dd, de) * bb2;
-  }
-  const T dab = T(2) * mb0 - pb2 + ub0 + vb0;
-  const T dbb = -T(7) * mb0 - mb1 + T(2) * pb1 + T(5) * pb2 - T(2) * ub0 - T(4) * vb0 + ub1 + vb1;
-  const T ddb = T(2) * mb1 + T(5) * mb2 - T(7) * pb0 - pb1 + ub1 - vb1 - T(2) * ub2 - T(4) * vb2;
-  const T deb = -mb2 + T(2) * pb0 + ub2 + vb2;
-  g[0] = dab;
-  g[1] = dbb;
-  g[2] = gm + gp - (dab + dbb + ddb + deb);
-  g[3] = ddb;
-  g[4] = deb;
 }
 
 // ---------------------------------------------------------------------------
@@ -226,7 +69,7 @@ __device__ __forceinline__ void weno5_rev(T a, T b, T c, T d, T e, bool linear,
 //   Sb_j = -2 (mb_j (m_j - Mm) + pb_{2-j} (p_{2-j} - Mp)) / S_j,
 // where mb_k = gm w_k / 6 and pb_k = gp wp_k / 6 are the cotangents of the
 // candidate values, and those of u_j and v_j are Sb_j (26/3) u_j and Sb_j 2 v_j
-// (dS/du = (26/3) u, dS/dv = 2 v). The weights are formed as in weno5_lin.
+// (dS/du = (26/3) u, dS/dv = 2 v). The weights are formed as in weno5_cell.
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void weno5_linrev(T a, T b, T c, T d, T e, T eps, bool linear, T gm,
@@ -758,312 +601,327 @@ __device__ __forceinline__ void riemann_flux_adj(const T (&xl)[NV], const T (&xr
 // kernels
 // ---------------------------------------------------------------------------
 
-// ---------------------------------------------------------------------------
-// Fused adjoint of one direction d for a tile of LN lines x TL cells along d.
-// In LDS: (A) left/right face states of the reconstructed cells the tile
-// needs, (B) LMARS forward and reverse at its faces with the flux cotangent
-// from r_bar, (C) WENO5 reverse of its reconstructed cells (the cotangents of
-// their five inputs), (D) for every cell of the tile (and the ghost cells
-// beyond a domain edge) the fixed-order sum of the contributions that reach
-// it, added into the primitive cotangent P. Deterministic: every sum has one
-// fixed order and the directions run as separate launches.
-// ---------------------------------------------------------------------------
-template <typename T, int NV, int LN, int TL>
-struct LineTile {
-  static constexpr int NA = TL + 6;   // reconstructed cells -3 .. TL+2 (relative)
-  static constexpr int NF = TL + 5;   // faces -2 .. TL+2
-  static constexpr int NC = TL + 4;   // reverse-reconstructed cells -2 .. TL+1
-  // threads: the largest phase (NA items per line) in one round of whole waves
-  static constexpr int NTHR = (LN * NA + 63) / 64 * 64;
-  // the face states are dead once (B) has read them: (C) writes over them
-  union {
-    struct {
-      T QM[NV][LN][NA];   // left state at face j+1 of reconstructed cell j
-      T QP[NV][LN][NA];   // right state at face j
-    };
-    T C[5][NV][LN][NC];   // cotangents of the five inputs of reconstructed cell j
-  };
-  T XL[NV][LN][NF];   // cotangent of the left state at face f
-  T XR[NV][LN][NF];   // cotangent of the right state at face f
-  T WL[NV][LN][TL + 10];   // primitives of cells -5 .. TL+4 (relative), the stencils of (A) and (C)
-  long long pbase[LN];  // padded offset of position 0 of each line
-  long long rbase[LN];  // interior offset of position 0 of each line
-  int lev[LN];          // level (z index) of each line (x and y lines)
-};
-
-// Tile shape per element type, variable count and direction (x lines are
-// contiguous; y and z lines are consecutive in x): 3 x lines of 64 cells and
-// 8 y / z lines of 16 cells, or shorter lines where that tile would exceed
-// 64 KiB of LDS. Small tiles let four to six workgroups share a compute unit;
-// on the single-precision 256 x 256 x 128 right-hand-side adjoint they took
-// 1.61 ms against 2.17 ms for 4 x 64 and 8 x 32 cells, the halo work they add
-// notwithstanding. Three x lines rather than two put 210 of the (A)-phase
-// items on 256 threads instead of 140 on 192 (1.47 -> 1.40 ms; 4 x 32, 5 x 32,
-// 6 x 32, 10 x 32 and 4 x 64 measured slower or even).
-#ifndef SNAP_ADJ_XLN
-#define SNAP_ADJ_XLN 3
-#endif
-#ifndef SNAP_ADJ_XTL
-#define SNAP_ADJ_XTL 64
-#endif
-#ifndef SNAP_ADJ_YLN
-#define SNAP_ADJ_YLN 8
-#endif
-#ifndef SNAP_ADJ_YTL
-#define SNAP_ADJ_YTL 16
-#endif
-template <typename T, int NV, bool XDIR>
-struct LineShape {
-  static constexpr int L0 = XDIR ? SNAP_ADJ_XLN : SNAP_ADJ_YLN;
-  static constexpr int T0 = XDIR ? SNAP_ADJ_XTL : SNAP_ADJ_YTL;
-  static constexpr bool A = sizeof(LineTile<T, NV, L0, T0>) <= 65536;
-  static constexpr bool B = sizeof(LineTile<T, NV, L0, T0 / 2>) <= 65536;
-  static constexpr int LN = A || B ? L0 : (L0 + 1) / 2;
-  static constexpr int TL = A ? T0 : T0 / 2;
-};
-
-struct LineGeom {
-  int d;          // direction
-  int nd;         // cells along d
-  long long nlines;
-  long long sd;   // padded stride along d
-  long long rd;   // interior stride along d
-};
-
-__host__ __device__ inline LineGeom line_geom(const AdjArgs& a, int d) {
-  LineGeom g;
-  g.d = d;
-  g.nd = d == 0 ? a.nx : (d == 1 ? a.ny : a.nz);
-  g.nlines = d == 0 ? (long long)a.ny * a.nz : (d == 1 ? (long long)a.nx * a.nz : (long long)a.nx * a.ny);
-  g.sd = d == 0 ? 1 : (d == 1 ? a.sy : a.sz);
-  g.rd = d == 0 ? 1 : (d == 1 ? a.ry : a.rz);
-  return g;
+// Conserved cotangent of one cell of the stencil region (interior
+// coordinates; ghost cells lie outside the domain along one axis at most),
+// in double precision: gravity terms (interior cells only) and the reverse of
+// the conserved -> primitive map applied to the primitive cotangent pb (P).
+// Passive gas: p = (gamma - 1)(E - K). Mixture (MIX, App. B):
+// p = (gamma - 1)(n / d)((E - K) - A) with n = 1 + sum a_t q_t,
+// d = 1 + sum b_t q_t, A = sum mu_t rho_t and q_t = rho_t / rho; with
+// Qb = (gamma - 1)(n / d) pb_p the cotangents of E, of the momenta through K
+// and of the tracer densities through A are Qb, -Qb u_i and -Qb mu_t, and
+// n / d adds ((gamma - 1) Q pb_p)(a_t / d - b_t n / d^2) to each fraction's
+// cotangent, Q = (E - K) - A. The passive form is the case n = d = 1, A = 0.
+template <typename T, int NV, bool MIX>
+__device__ __forceinline__ void adj_cons_from(const T* __restrict__ q, double (&pb)[NV],
+                                              const T* __restrict__ rb, const AdjArgs& a, int i,
+                                              int j, int k, double (&out)[NV]) {
+  const long long c = padded_off(a, i, j, k);
+  double cv[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) cv[v] = static_cast<double>(q[c + v * a.sv]);
+  double qe = 0.0;   // extra conserved cotangent of rho w from the energy source
+  const bool inside = i >= 0 && i < a.nx && j >= 0 && j < a.ny && k >= 0 && k < a.nz;
+  if (inside) {
+    const long long ro = (long long)k * a.rz + (long long)j * a.ry + i;
+    pb[0] += -a.grav * static_cast<double>(rb[ro + 3 * a.rv]);   // R_rhow -= g rho'
+    qe = -a.grav * static_cast<double>(rb[ro + 4 * a.rv]);       // R_E -= g rho w
+  }
+  // rho of the cell (perturbation storage: the stored value plus rhobar of its level)
+  const double inv = 1.0 / (cv[0] + (a.pert ? a.rbar_c[k + NG] : 0.0));
+  const double u = cv[1] * inv, v = cv[2] * inv, w = cv[3] * inv;
+  double Qb = a.gm1 * pb[4];   // cotangent of (E - K) - A
+  double fb[NV];               // extra cotangents of the fractions (mixture)
+#pragma unroll
+  for (int t = 5; t < NV; ++t) fb[t] = 0.0;
+  if constexpr (MIX) {
+    constexpr int NT = NV - 5;
+    double num = 1.0, den = 1.0, A = 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const double qt = cv[5 + t] * inv;
+      num += a.mix.a[t] * qt;
+      den += a.mix.b[t] * qt;
+      A += a.mix.mu[t] * cv[5 + t];
+    }
+    const double K = 0.5 * (cv[1] * u + cv[2] * v + cv[3] * w);
+    const double R = num / den, Q = (cv[4] - K) - A;
+    const double Rb = a.gm1 * Q * pb[4];
+    Qb = a.gm1 * R * pb[4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fb[5 + t] = Rb * (a.mix.a[t] - a.mix.b[t] * R) / den;
+  }
+  // p from E - K: dp/drho = Qb |u|^2 / 2, dp/dm = -Qb u
+  double rhob = pb[0] - (u * pb[1] + v * pb[2] + w * pb[3]) * inv +
+                Qb * 0.5 * (u * u + v * v + w * w);
+#pragma unroll
+  for (int t = 5; t < NV; ++t) {
+    const double qt = cv[t] * inv;
+    const double tb = pb[t] + fb[t];
+    rhob -= qt * tb * inv;
+    out[t] = tb * inv;
+    if constexpr (MIX) out[t] -= Qb * a.mix.mu[t - 5];
+  }
+  out[0] = rhob;
+  out[1] = pb[1] * inv - Qb * u;
+  out[2] = pb[2] * inv - Qb * v;
+  out[3] = pb[3] * inv - Qb * w + qe;
+  out[4] = Qb;
 }
 
-// interior coordinates (i, j, k) of position p on line L of direction d;
-// lines are numbered with the lower transverse axis fastest
-__device__ __forceinline__ void line_cell(const AdjArgs& a, const LineGeom& g, long long L, int p,
-                                          int& i, int& j, int& k) {
-  const int n0 = g.d == 0 ? a.ny : a.nx;
-  int lo, hi;
-  if (g.nlines <= 0xffffffffLL) {
-    const unsigned u = (unsigned)L, qq = u / (unsigned)n0;
-    hi = (int)qq;
-    lo = (int)(u - qq * (unsigned)n0);
-  } else {
-    hi = (int)(L / n0);
-    lo = (int)(L - (long long)hi * n0);
-  }
-  if (g.d == 0) {
-    i = p;
-    j = lo;
-    k = hi;
-  } else if (g.d == 1) {
-    i = lo;
-    j = p;
-    k = hi;
-  } else {
-    i = lo;
-    j = hi;
-    k = p;
+template <typename T, int NV, bool MIX>
+__device__ __forceinline__ void adj_cons_cell(const T* __restrict__ q, const T* __restrict__ P,
+                                              const T* __restrict__ rb, const AdjArgs& a, int i,
+                                              int j, int k, double (&out)[NV]) {
+  const long long c = padded_off(a, i, j, k);
+  double pb[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) pb[v] = static_cast<double>(P[c + v * a.sv]);
+  adj_cons_from<T, NV, MIX>(q, pb, rb, a, i, j, k, out);
+}
+
+// Where a cell's conserved cotangent goes: out (interior layout) overwritten
+// (mode 0), added to (mode 1), out = alpha * out + beta * result (mode 2), out =
+// alpha * rb + beta * result (mode 3; out and rb distinct), or out = alpha * out
+// + gam * y + rb + beta * result (mode 4: the last stage of the RK3 adjoint with
+// its three-term combination; out, y, rb distinct). fold: by the z direction
+// (lane kernel) for the cells at least 3 from the y and z edges.
+template <typename T>
+struct FoldOut {
+  T* out;
+  const T* y;
+  int mode, fold;
+  double alpha, beta, gam;
+};
+template <typename T, int NV>
+__device__ __forceinline__ void fold_store(const FoldOut<T>& f, const T* __restrict__ rb,
+                                           const AdjArgs& a, long long c,
+                                           const double (&acc)[NV]) {
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const long long o = c + v * a.rv;
+    if (f.mode == 0)
+      f.out[o] = static_cast<T>(acc[v]);
+    else if (f.mode == 1)
+      f.out[o] = static_cast<T>(static_cast<double>(f.out[o]) + acc[v]);
+    else if (f.mode == 2)
+      f.out[o] = static_cast<T>(f.alpha * static_cast<double>(f.out[o]) + f.beta * acc[v]);
+    else if (f.mode == 3)
+      f.out[o] = static_cast<T>(f.alpha * static_cast<double>(rb[o]) + f.beta * acc[v]);
+    else
+      f.out[o] = static_cast<T>(f.alpha * static_cast<double>(f.out[o]) +
+                                f.gam * static_cast<double>(f.y[o]) +
+                                static_cast<double>(rb[o]) + f.beta * acc[v]);
   }
 }
 
-// Optional occupancy target of the fused direction kernel (waves per SIMD);
-// 0 leaves the register budget to the compiler.
-#ifndef SNAP_ADJ_LINE_WAVES_PER_EU
-#define SNAP_ADJ_LINE_WAVES_PER_EU 0
-#endif
-#if SNAP_ADJ_LINE_WAVES_PER_EU > 0
-#define SNAP_ADJ_LINE_ATTR __attribute__((amdgpu_waves_per_eu(SNAP_ADJ_LINE_WAVES_PER_EU)))
-#else
-#define SNAP_ADJ_LINE_ATTR
-#endif
+// ---------------------------------------------------------------------------
+// Adjoint of one direction D (0 = x, 1 = y, 2 = z) with the cells of a line in
+// the lanes of a wave: a wave holds 64 consecutive cells of one line, every
+// lane the primitives of its cell, and what a cell needs of its neighbours (the
+// stencil of its reconstruction, the left state and r_bar at its lower face,
+// the cotangent at its upper face, the contributions of the four neighbouring
+// reconstructions) comes through lane shifts. So nothing waits at a barrier in
+// between, only one variable's WENO quantities are live at a time, and the
+// registers grow by about five values per variable, where a tile that keeps
+// them in registers from the forward to the reverse phase takes twelve and
+// spilled from nine variables on in double precision.
+// Per lane: (1) both face values of its cell (weno5_cell); (2) the Riemann flux
+// forward and reverse at its lower face with the flux cotangent (r_bar[c] -
+// r_bar[c-1]) / dx; (3) the WENO5 reverse of its cell (weno5_linrev) and the sum
+// of the five contributions that reach it, in a fixed order: reproducible bit
+// for bit. A wave writes the 54 cells whose contributions it holds whole.
+// y and z lines are loaded and stored through LDS, lane_waves of them
+// consecutive in x per workgroup, so that memory is accessed along x.
+// The x direction overwrites P on every cell of the interior rows (ghosts
+// included); y and z add to it, and overwrite it on the ghost cells beyond
+// their own edges, which they reach first.
+// fo: with fo.fold (z direction, after k_adj_xmerge) a cell at least 3 from the
+// y and z edges is complete here, and its conserved cotangent is formed and
+// stored instead of P (k_adj_consfold then takes the rows that are left).
+// Grid: the segments (lane_segments) of the positions -3 .. nd + 2, and in a
+// segment the line groups (x: lines (j, k), a line per wave; y, z: groups of
+// lane_waves lines, x fastest).
+// 256 x 256 x 128, one gradient step in double precision (kept stages): 12.45 ms
+// with tiles of lines in LDS and five barriers per direction, 8.9 ms now; the
+// x direction of 101 x 84 x 64 66 -> 39 us, y 82 -> 55; seven variables on
+// 160 x 160 x 80 6.22 -> 3.10 ms; the mixture with six tracers on 96 x 80 x 64
+// 233 (spilled) -> 137 us in y.
+// ---------------------------------------------------------------------------
+// 64 lanes less a halo of 5 on either side; beyond an end of the line two lanes
+// that contribute nothing take the halo's place, and the first and the last
+// segment write 57 cells (a single segment 60).
+constexpr int LANE_OUT = 54;
+__host__ __device__ constexpr int lane_segments(int nd) {
+  return (nd + LANE_OUT - 1) / LANE_OUT;
+}
 
-template <typename T, int NV, int LN, int TL, bool XDIR, bool HLLC = false, bool MIX = false>
-__global__ void __launch_bounds__((LineTile<T, NV, LN, TL>::NTHR)) SNAP_ADJ_LINE_ATTR
-    k_adj_line(const T* __restrict__ q, const T* __restrict__ rb, AdjArgs a, int d,
-               T* __restrict__ P) {
-  using Tile = LineTile<T, NV, LN, TL>;
-  constexpr int NTHR = Tile::NTHR;
-  static_assert(NTHR >= LN * Tile::NA, "one item of phase A per thread");
-  __shared__ Tile S;
-  const LineGeom g = line_geom(a, d);
-  const unsigned nseg = (unsigned)((g.nd + TL - 1) / TL);
-  const unsigned lt = blockIdx.x / nseg;
-  const int seg = (int)(blockIdx.x - lt * nseg);
-  const long long L0 = (long long)lt * LN;
-  const int c0 = seg * TL;
-  const int c1 = min(c0 + TL, g.nd);
+// Lines per workgroup: 32 bytes of every row for y and z. Neighbouring groups
+// meet in one XCD's L2, and small workgroups overlap their barriers: with 64
+// bytes the six-tracer mixture step of 96 x 80 x 64 in double precision took
+// 2078 us against 1889, the gradient of 101 x 84 x 64 3334 against 3237.
+template <typename T, int D>
+constexpr int lane_waves() {
+  return D == 0 ? 4 : (int)(32 / sizeof(T));
+}
+
+__device__ __forceinline__ float lane_shift(float x, int addr) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(x)));
+}
+__device__ __forceinline__ double lane_shift(double x, int addr) {
+  const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(x));
+  const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(x));
+  return __hiloint2double(hi, lo);
+}
+
+template <typename T, int NV, int D, bool HLLC, bool MIX>
+__global__ void __launch_bounds__((64 * lane_waves<T, D>()))
+    k_adj_lane(const T* __restrict__ q, const T* __restrict__ rb, AdjArgs a, int nseg,
+               T* __restrict__ P, FoldOut<T> fo) {
+  constexpr int NW = lane_waves<T, D>();
+  // a line in LDS, padded so that the NW x (64 / NW) elements a wave stores fall
+  // on different banks
+  constexpr int ROW = sizeof(T) == 4 ? 72 : 80;
+  __shared__ T S[D == 0 ? 1 : NV][D == 0 ? 1 : NW][D == 0 ? 1 : ROW];
+  const int nd = D == 0 ? a.nx : (D == 1 ? a.ny : a.nz);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // consecutive line groups on one XCD: neighbours in x share cache lines
+  const int L = xcd_logical_block(blockIdx.x, gridDim.x), ng = gridDim.x / nseg;
+  const int seg = L / ng, grp = L - seg * ng;
+  const int c_lo = seg == 0 ? -3 : LANE_OUT * seg;
+  const int c_hi = seg == nseg - 1 ? nd + 3 : LANE_OUT * (seg + 1);
+  const int c0 = seg == 0 ? -5 : c_lo - 5;   // the cell of lane 0
+  const int cg = c0 + lane;
+  const long long sd = D == 0 ? 1 : (D == 1 ? a.sy : a.sz);
+  const long long rd = D == 0 ? 1 : (D == 1 ? a.ry : a.rz);
+  // the line this wave computes (lev: its level, x and y lines), and for y and
+  // z the (position, line) this thread loads and stores
+  const int n0 = D == 0 ? a.ny : (a.nx + NW - 1) / NW;   // groups (x: lines) per row
+  const int o1 = D == 0 ? 0 : grp / n0, g0 = (D == 0 ? 0 : grp % n0) * NW;
+  const long long nl = (long long)a.ny * a.nz;
+  const long long line = D == 0 ? min((long long)grp * NW + wv, nl - 1) : 0;
+  const bool mine = D == 0 ? (long long)grp * NW + wv < nl : true;
+  const int jx = (int)(D == 0 ? line % a.ny : 0), kx = (int)(D == 0 ? line / a.ny : 0);
+  const int mp = D == 0 ? lane : threadIdx.x / NW, mi = D == 0 ? 0 : g0 + threadIdx.x % NW;
+  const int ml = D == 0 ? 0 : threadIdx.x % NW;
+  const int mc = c0 + mp;   // the position this thread loads and stores
+  const int lev = D == 0 ? kx : (D == 1 ? o1 : 0);
+  const int is = min(mi, a.nx - 1);
+  const long long pb = D == 0 ? padded_off(a, 0, jx, kx)
+                              : (D == 1 ? padded_off(a, is, 0, o1) : padded_off(a, is, o1, 0));
+  const long long rbo = D == 0   ? (long long)kx * a.rz + (long long)jx * a.ry
+                        : D == 1 ? (long long)o1 * a.rz + is
+                                 : (long long)o1 * a.ry + is;
   const T eps = static_cast<T>(a.eps), gamma = static_cast<T>(a.gamma);
-  // constant indices only: a runtime index into the argument struct would
-  // copy it to scratch memory
-  const T inv_gm1 = static_cast<T>(a.inv_gm1);
-  const T hi = static_cast<T>(d == 0 ? a.dxi[0] : (d == 1 ? a.dxi[1] : a.dxi[2]));
+  const T inv_gm1 = static_cast<T>(a.inv_gm1), hi = static_cast<T>(a.dxi[D]);
   const bool linear = a.linear != 0;
-  // item (l, p) of a phase with np positions: x lines run p fastest, y/z lines l fastest
-  auto decode = [&](int it, int np, int& l, int& p) {
-    if (XDIR) {
-      l = it / np;
-      p = it % np;
-    } else {
-      l = it % LN;
-      p = it / LN;
-    }
-  };
-  // line tables: offsets of position 0 of every line of the tile
-  if (threadIdx.x < LN && L0 + threadIdx.x < g.nlines) {
-    int i, j, k;
-    line_cell(a, g, L0 + threadIdx.x, 0, i, j, k);
-    S.pbase[threadIdx.x] = padded_off(a, i, j, k);
-    S.rbase[threadIdx.x] = (long long)k * a.rz + (long long)j * a.ry + i;
-    S.lev[threadIdx.x] = k;
-  }
-  __syncthreads();
-  // (A) this thread's reconstructed cell jg = c0-3+pa (one per thread, -1 .. nd);
-  // the forward quantities stay in registers for its reverse in (C)
-  int la, pa;
-  decode(threadIdx.x, Tile::NA, la, pa);
-  const bool line_a = threadIdx.x < LN * Tile::NA && L0 + la < g.nlines;
-  const int ja = c0 - 3 + pa;
-  const bool cell_a = line_a && ja >= -1 && ja <= g.nd;
-  WenoLin<T> lin[NV];
-  // the primitives of the tile's lines, cells c0-5 .. c0+TL+4 (those outside
-  // the padded range -3 .. nd+2 are never read), converted from the
-  // ghost-filled state and staged in LDS once: the stencils of (A) and (C)
-  // are read from there
-  for (int it = threadIdx.x; it < LN * (TL + 10); it += NTHR) {
-    int l, m;
-    decode(it, TL + 10, l, m);
-    const int jg = c0 - 5 + m;
-    if (L0 + l < g.nlines && jg >= -3 && jg <= g.nd + 2) {
-      const long long pc = S.pbase[l] + jg * g.sd;
-      const int kl = d == 2 ? jg : S.lev[l];   // level of the cell
-      T x[NV];
-      load_prim<T, NV, MIX>(q, pc, a.sv, level_ref(a.pert, a.rbar_c[kl + NG], a.pbar_c[kl + NG]),
-                            a.gm1, a.mix, x);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) S.WL[v][l][m] = x[v];
-    }
-  }
-  __syncthreads();
-  // cell ja = c0-3+pa uses cells ja-2 .. ja+2, positions pa .. pa+4 of WL
-  auto load_stencils = [&](T (&st)[NV][5]) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-#pragma unroll
-      for (int o = 0; o < 5; ++o) st[v][o] = S.WL[v][la][pa + o];
-  };
-  if (cell_a) {
-    T st[NV][5];
-    load_stencils(st);
+  T x[NV], r[NV];
+  {
+    // positions outside the padded range read the nearest cell: nothing of
+    // them reaches a cell that is written
+    const int cc = min(max(mc, -3), nd + 2);
+    const int kl = D == 2 ? cc : lev;
+    load_prim<T, NV, MIX>(q, pb + cc * sd, a.sv,
+                          level_ref(a.pert, a.rbar_c[kl + NG], a.pbar_c[kl + NG]), a.gm1, a.mix, x);
+    const bool in = mc >= 0 && mc < nd;
+    const long long ro = rbo + min(max(mc, 0), nd - 1) * rd;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      T qm, qp;
-      weno5_lin<T>(st[v][0], st[v][1], st[v][2], st[v][3], st[v][4], eps, linear, lin[v], qm, qp);
-      S.QM[v][la][pa] = qm;
-      S.QP[v][la][pa] = qp;
+      const T y = rb[ro + v * a.rv];
+      r[v] = in ? y : T(0);
     }
   }
-  __syncthreads();
-  // (B) LMARS forward + reverse at faces f = c0-2 .. c0+TL+2 that exist (0 .. nd)
-  for (int it = threadIdx.x; it < LN * Tile::NF; it += NTHR) {
-    int l, p;
-    decode(it, Tile::NF, l, p);
-    const int fg = c0 - 2 + p;
-    if (L0 + l >= g.nlines) continue;
-    T xlb[NV], xrb[NV];
+  if constexpr (D != 0) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      xlb[v] = T(0);
-      xrb[v] = T(0);
+    for (int v = 0; v < NV; ++v) S[v][ml][mp] = x[v];
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) x[v] = S[v][wv][lane];
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) S[v][ml][mp] = r[v];
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) r[v] = S[v][wv][lane];
+  }
+  const int dn1 = ((lane - 1) & 63) * 4, dn2 = ((lane - 2) & 63) * 4;
+  const int up1 = ((lane + 1) & 63) * 4, up2 = ((lane + 2) & 63) * 4;
+  // (1) face values of the cell: xr the right state of its lower face, xl (from
+  // the lane below) the left state of that face
+  T xl[NV], xr[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    T qm;
+    weno5_cell<T>(lane_shift(x[v], dn2), lane_shift(x[v], dn1), x[v], lane_shift(x[v], up1),
+                  lane_shift(x[v], up2), eps, linear, qm, xr[v]);
+    xl[v] = lane_shift(qm, dn1);
+    r[v] = (r[v] - lane_shift(r[v], dn1)) * hi;   // flux cotangent of the lower face
+  }
+  // (2) the lower face, 0 .. nd
+  T xlb[NV], xrb[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    xlb[v] = T(0);
+    xrb[v] = T(0);
+  }
+  if (cg >= 0 && cg <= nd) {
+    const T rref = static_cast<T>(D == 2 ? a.rbar_f[cg] : a.rbar_c[lev + NG]);
+    const T pref = static_cast<T>(D == 2 ? a.pbar_f[cg] : a.pbar_c[lev + NG]);
+    riemann_flux_adj<T, NV, HLLC, MIX>(xl, xr, D + 1, rref, pref, gamma, inv_gm1,
+                                       static_cast<T>(a.gm1), a.mix, r, xlb, xrb);
+  }
+  // (3) the reverse of the cell's reconstruction (cells -1 .. nd) and the sum
+  // of what reaches it
+  const bool rec = cg >= -1 && cg <= nd;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    // opaque, so that the stencil is shifted in again rather than its four
+    // values of every variable kept from (1): 8 registers per variable in
+    // double precision, which decide the waves per SIMD
+    asm volatile("" : "+v"(x[v]));
+    const T gm = lane_shift(xlb[v], up1);
+    T g[5];
+    weno5_linrev<T>(lane_shift(x[v], dn2), lane_shift(x[v], dn1), x[v], lane_shift(x[v], up1),
+                    lane_shift(x[v], up2), eps, linear, gm, xrb[v], g);
+#pragma unroll
+    for (int o = 0; o < 5; ++o) g[o] = rec ? g[o] : T(0);
+    x[v] = (((lane_shift(g[0], up2) + lane_shift(g[1], up1)) + g[2]) + lane_shift(g[3], dn1)) +
+           lane_shift(g[4], dn2);
+    // opaque: the sum is formed here, not its five terms of every variable
+    // kept until the store (20 registers per variable in double precision). In x
+    // with up to 7 variables, where no LDS round trip waits before the store,
+    // the longer stretch without it is the faster (x with, without: one gradient
+    // of 256 x 256 x 128 in single precision 4175, 3999 us; 7 variables on
+    // 160 x 160 x 80 in double 3192, 3096; the six-tracer mixture 1907, 2002)
+    if constexpr (D != 0 || NV > 7) asm volatile("" : "+v"(x[v]));
+  }
+  if constexpr (D == 0) {
+    if (mine && cg >= c_lo && cg < c_hi) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) P[pb + cg + v * a.sv] = x[v];
     }
-    if (fg >= 0 && fg <= g.nd) {
-      T xl[NV], xr[NV], fbar[NV];
-      // face fg: left state = qm of cell fg-1 (index p), right = qp of cell fg (index p+1)
+  } else {
+    __syncthreads();
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        xl[v] = S.QM[v][l][p];
-        xr[v] = S.QP[v][l][p + 1];
-      }
-      const long long ro = S.rbase[l] + (fg < g.nd ? fg : g.nd - 1) * g.rd;   // cell min(fg, nd-1)
+    for (int v = 0; v < NV; ++v) S[v][wv][lane] = x[v];
+    __syncthreads();
+    if (mi < a.nx && mc >= c_lo && mc < c_hi) {
+      const bool add = mc >= 0 && mc < nd;
+      T* p = P + (pb + mc * sd);
+      T old[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const T right = fg < g.nd ? rb[ro + v * a.rv] : T(0);
-        const long long lo = fg < g.nd ? ro - g.rd : ro;   // cell fg-1
-        const T left = fg > 0 ? rb[lo + v * a.rv] : T(0);
-        fbar[v] = (right - left) * hi;
-      }
-      T rref, pref;
-      if (d == 2) {
-        rref = static_cast<T>(a.rbar_f[fg]);
-        pref = static_cast<T>(a.pbar_f[fg]);
+      for (int v = 0; v < NV; ++v) old[v] = add ? p[v * a.sv] : T(0);
+      if (D == 2 && fo.fold && mc >= 3 && mc < nd - 3 && (!a.d3 || (o1 >= 3 && o1 < a.ny - 3))) {
+        double pb[NV], acc[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) pb[v] = static_cast<double>(old[v] + S[v][ml][mp]);
+        adj_cons_from<T, NV, MIX>(q, pb, rb, a, mi, o1, mc, acc);
+        fold_store<T, NV>(fo, rb, a, rbo + mc * rd, acc);
       } else {
-        rref = static_cast<T>(a.rbar_c[S.lev[l] + NG]);
-        pref = static_cast<T>(a.pbar_c[S.lev[l] + NG]);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) p[v * a.sv] = old[v] + S[v][ml][mp];
       }
-      riemann_flux_adj<T, NV, HLLC, MIX>(xl, xr, d + 1, rref, pref, gamma, inv_gm1,
-                                         static_cast<T>(a.gm1), a.mix, fbar, xlb, xrb);
     }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      S.XL[v][l][p] = xlb[v];
-      S.XR[v][l][p] = xrb[v];
-    }
-  }
-  __syncthreads();
-  // (C) WENO5 reverse of the same cell: C index pa-1 covers cells c0-2 .. c0+TL+1
-  if (line_a && pa >= 1 && pa <= Tile::NC) {
-    const int pc = pa - 1;
-    if (cell_a) {
-      T st[NV][5];
-      load_stencils(st);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        // qm_j is the left state of face j+1 (XL index pc+1); qp_j the right state of face j (XR index pc)
-        const T gm = S.XL[v][la][pc + 1];
-        const T gp = S.XR[v][la][pc];
-        T out[5];
-        weno5_rev<T>(st[v][0], st[v][1], st[v][2], st[v][3], st[v][4], linear, lin[v], gm, gp,
-                     out);
-#pragma unroll
-        for (int o = 0; o < 5; ++o) S.C[o][v][la][pc] = out[o];
-      }
-    } else {
-#pragma unroll
-      for (int o = 0; o < 5; ++o)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) S.C[o][v][la][pc] = T(0);
-    }
-  }
-  __syncthreads();
-  // (D) cells of the tile, plus the ghost cells beyond a domain edge
-  const int lo = c0 == 0 ? -3 : c0;
-  const int hiend = c1 == g.nd ? g.nd + 3 : c1;
-  const int npos = hiend - lo;
-  for (int it = threadIdx.x; it < LN * (TL + 6); it += NTHR) {
-    int l, p;
-    decode(it, TL + 6, l, p);
-    if (p >= npos || L0 + l >= g.nlines) continue;
-    const int cg = lo + p;
-    const long long pc = S.pbase[l] + cg * g.sd;
-    // the first direction kernel to reach a cell starts its sum from zero: x
-    // reaches every cell of the interior rows (x ghosts included), y and z
-    // the ghost cells beyond their own edges first (no zero-fill pass)
-    const bool first = XDIR || cg < 0 || cg >= g.nd;
-    T acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = first ? T(0) : P[pc + v * a.sv];
-#pragma unroll
-    for (int o = 0; o < 5; ++o) {
-      const int jg = cg + 2 - o;   // reconstruction whose input o is this cell
-      if (jg < -1 || jg > g.nd) continue;
-      const int q = jg - (c0 - 2);   // its index in C
-#pragma unroll
-      for (int v = 0; v < NV; ++v) acc[v] += S.C[o][v][l][q];
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) P[pc + v * a.sv] = acc[v];
   }
 }
 
@@ -1074,7 +932,7 @@ __device__ __forceinline__ int adj_ghost_src(int idx, int n, int bc) {
   return max(2 * n - 1 - idx, 0);
 }
 
-// Before a folding z march (single precision, after the x direction): each
+// Before a folding z direction (after the x direction): each
 // interior cell within 3 of an x edge takes the primitive cotangents of the
 // ghost cells that copy it in x into its own (fixed order: low then high
 // ghost positions). A periodic copy holds the cell's state and a mirror copy
@@ -1371,77 +1229,6 @@ __global__ void __launch_bounds__(256, NV <= 5 ? 3 : 2) k_adj_march(const T* __r
   }
 }
 
-// Conserved cotangent of one cell of the stencil region (interior
-// coordinates; ghost cells lie outside the domain along one axis at most),
-// in double precision: gravity terms (interior cells only) and the reverse of
-// the conserved -> primitive map applied to the primitive cotangent P.
-// Passive gas: p = (gamma - 1)(E - K). Mixture (MIX, App. B):
-// p = (gamma - 1)(n / d)((E - K) - A) with n = 1 + sum a_t q_t,
-// d = 1 + sum b_t q_t, A = sum mu_t rho_t and q_t = rho_t / rho; with
-// Qb = (gamma - 1)(n / d) pb_p the cotangents of E, of the momenta through K
-// and of the tracer densities through A are Qb, -Qb u_i and -Qb mu_t, and
-// n / d adds ((gamma - 1) Q pb_p)(a_t / d - b_t n / d^2) to each fraction's
-// cotangent, Q = (E - K) - A. The passive form is the case n = d = 1, A = 0.
-template <typename T, int NV, bool MIX>
-__device__ __forceinline__ void adj_cons_cell(const T* __restrict__ q, const T* __restrict__ P,
-                                              const T* __restrict__ rb, const AdjArgs& a, int i,
-                                              int j, int k, double (&out)[NV]) {
-  const long long c = padded_off(a, i, j, k);
-  double pb[NV], cv[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    pb[v] = static_cast<double>(P[c + v * a.sv]);
-    cv[v] = static_cast<double>(q[c + v * a.sv]);
-  }
-  double qe = 0.0;   // extra conserved cotangent of rho w from the energy source
-  const bool inside = i >= 0 && i < a.nx && j >= 0 && j < a.ny && k >= 0 && k < a.nz;
-  if (inside) {
-    const long long ro = (long long)k * a.rz + (long long)j * a.ry + i;
-    pb[0] += -a.grav * static_cast<double>(rb[ro + 3 * a.rv]);   // R_rhow -= g rho'
-    qe = -a.grav * static_cast<double>(rb[ro + 4 * a.rv]);       // R_E -= g rho w
-  }
-  // rho of the cell (perturbation storage: the stored value plus rhobar of its level)
-  const double inv = 1.0 / (cv[0] + (a.pert ? a.rbar_c[k + NG] : 0.0));
-  const double u = cv[1] * inv, v = cv[2] * inv, w = cv[3] * inv;
-  double Qb = a.gm1 * pb[4];   // cotangent of (E - K) - A
-  double fb[NV];               // extra cotangents of the fractions (mixture)
-#pragma unroll
-  for (int t = 5; t < NV; ++t) fb[t] = 0.0;
-  if constexpr (MIX) {
-    constexpr int NT = NV - 5;
-    double num = 1.0, den = 1.0, A = 0.0;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const double qt = cv[5 + t] * inv;
-      num += a.mix.a[t] * qt;
-      den += a.mix.b[t] * qt;
-      A += a.mix.mu[t] * cv[5 + t];
-    }
-    const double K = 0.5 * (cv[1] * u + cv[2] * v + cv[3] * w);
-    const double R = num / den, Q = (cv[4] - K) - A;
-    const double Rb = a.gm1 * Q * pb[4];
-    Qb = a.gm1 * R * pb[4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) fb[5 + t] = Rb * (a.mix.a[t] - a.mix.b[t] * R) / den;
-  }
-  // p from E - K: dp/drho = Qb |u|^2 / 2, dp/dm = -Qb u
-  double rhob = pb[0] - (u * pb[1] + v * pb[2] + w * pb[3]) * inv +
-                Qb * 0.5 * (u * u + v * v + w * w);
-#pragma unroll
-  for (int t = 5; t < NV; ++t) {
-    const double qt = cv[t] * inv;
-    const double tb = pb[t] + fb[t];
-    rhob -= qt * tb * inv;
-    out[t] = tb * inv;
-    if constexpr (MIX) out[t] -= Qb * a.mix.mu[t - 5];
-  }
-  out[0] = rhob;
-  out[1] = pb[1] * inv - Qb * u;
-  out[2] = pb[2] * inv - Qb * v;
-  out[3] = pb[3] * inv - Qb * w + qe;
-  out[4] = Qb;
-}
-
 // ---------------------------------------------------------------------------
 // Reverse of the sedimentation terms (Sec. 2; sediment_cell in the stage
 // kernels): condensate t with vertical velocity w_t carries through every z
@@ -1532,21 +1319,14 @@ __global__ void __launch_bounds__(256) k_adj_sediment(const T* __restrict__ q,
 // Per interior cell: its conserved cotangent plus those of the ghost cells
 // that copy it (fixed order: x, y, z; low then high; the reflected normal
 // momentum negated), computed in place from q and P, so no padded conserved
-// cotangent is written and read back. out: interior layout, overwritten
-// (mode 0), added to (mode 1), out = alpha * out + beta * result (mode 2),
-// out = alpha * rb + beta * result (mode 3; out and rb distinct), or
-// out = alpha * out + gam * y + rb + beta * result (mode 4: the last stage of
-// the RK3 adjoint with its three-term combination; out, y, rb distinct).
+// cotangent is written and read back; stored as FoldOut says.
 template <typename T, int NV, bool MIX = false>
 __global__ void __launch_bounds__(256) k_adj_consfold(const T* __restrict__ q,
                                                       const T* __restrict__ P,
                                                       const T* __restrict__ rb, AdjArgs a,
-                                                      T* __restrict__ out, int mode,
-                                                      double alpha, double beta,
-                                                      const T* __restrict__ y, double gam,
-                                                      int zedge) {
+                                                      FoldOut<T> fo, int zedge) {
   // grid: x over interior rows, y over the interior row. zedge (nz > 6, the
-  // z march having folded the rest, after k_adj_xmerge): only the rows of the
+  // z direction having folded the rest, after k_adj_xmerge): only the rows of the
   // 3 lowest and the 3 highest levels, then (3-D) the rows within 3 of a y
   // edge on the levels between
   const int i = blockIdx.y * 256 + threadIdx.x;
@@ -1587,21 +1367,7 @@ __global__ void __launch_bounds__(256) k_adj_consfold(const T* __restrict__ q,
       for (int v = 0; v < NV; ++v) acc[v] += (flip && v == 1 + d) ? -x[v] : x[v];
     }
   }
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const long long o = c + v * a.rv;
-    if (mode == 0)
-      out[o] = static_cast<T>(acc[v]);
-    else if (mode == 1)
-      out[o] = static_cast<T>(static_cast<double>(out[o]) + acc[v]);
-    else if (mode == 2)
-      out[o] = static_cast<T>(alpha * static_cast<double>(out[o]) + beta * acc[v]);
-    else if (mode == 3)
-      out[o] = static_cast<T>(alpha * static_cast<double>(rb[o]) + beta * acc[v]);
-    else
-      out[o] = static_cast<T>(alpha * static_cast<double>(out[o]) + gam * static_cast<double>(y[o]) +
-                              static_cast<double>(rb[o]) + beta * acc[v]);
-  }
+  fold_store<T, NV>(fo, rb, a, c, acc);
 }
 
 }  // namespace snap
