@@ -1033,6 +1033,7 @@ static int kessler_args(const snap_grid* g, double dt, const snap_kessler* k, Ke
     d.k4 = sp.k4;
     d.p_ref = sp.p_ref;
     d.t_ref = sp.t_ref;
+    d.it_ref = 1.0 / sp.t_ref;
     d.beta = sp.beta;
     d.delta = sp.delta;
     d.eps = g->tracer_eps[sp.vapour];
@@ -1050,12 +1051,14 @@ static int kessler_args(const snap_grid* g, double dt, const snap_kessler* k, Ke
   a.sv = a.sz * (g->nz + 2 * SNAP_NG);
   a.dt = dt;
   a.rd = k->rd;
+  a.ird = 1.0 / k->rd;
   a.tol = k->tol;
   a.gm1 = g->gamma - 1.0;
   a.m = mixture_of(g);
   for (int t = 0; t < g->ntracer; ++t) {
     a.vap[t] = g->tracer_kind[t] == SNAP_TRACER_VAPOUR ? 1 : 0;
     a.eps[t] = a.vap[t] ? g->tracer_eps[t] : 1.0;
+    a.ieps[t] = 1.0 / a.eps[t];
   }
   if ((long long)g->ny * g->nz > 0x7fffffffLL) return fail(SNAP_E_INVALID, "ny nz too large");
   return 0;
@@ -1118,6 +1121,7 @@ static int satadj_args(const snap_grid* g, const snap_satadj* sa, SatAdjArgs& a)
     d.c = sp.cloud;
     d.p_ref = sp.p_ref;
     d.t_ref = sp.t_ref;
+    d.it_ref = 1.0 / sp.t_ref;
     d.beta = sp.beta;
     d.delta = sp.delta;
     d.rv = sa->rd / g->tracer_eps[sp.vapour];
@@ -1138,6 +1142,11 @@ static int satadj_args(const snap_grid* g, const snap_satadj* sa, SatAdjArgs& a)
   for (int t = 0; t < g->ntracer; ++t) {
     a.sigma[t] = g->tracer_sigma[t];
     a.mu[t] = g->tracer_mu[t];
+  }
+  for (int sidx = 0; sidx < sa->nspecies; ++sidx) {
+    SatAdjSpec& d = a.s[sidx];
+    d.dmu = a.mu[d.c] - a.mu[d.v];
+    d.dcap = a.cvd * (a.sigma[d.c] - a.sigma[d.v]);
   }
   if ((long long)g->ny * g->nz > 0x7fffffffLL) return fail(SNAP_E_INVALID, "ny nz too large");
   return 0;

@@ -30,22 +30,24 @@ struct CflArgs {
 // Kessler microphysics (Sec. 3): one condensable species.
 struct KesslerSpec {
   int v, c, p;   // tracer indices of vapour, cloud, precipitation
-  double k1, k2, k3, k4, p_ref, t_ref, beta, delta, eps;
+  double k1, k2, k3, k4, p_ref, t_ref, it_ref, beta, delta, eps;   // it_ref = 1 / t_ref
 };
 
 struct KesslerArgs {
   int nx, ny, nz, gy, nspecies, max_iter;
   long long sy, sz, sv;
-  double dt, rd, tol, gm1;
+  double dt, rd, ird, tol, gm1;   // ird = 1 / rd
   Mixture m;                      // mixture coefficients of the pressure
   int vap[MAX_TRACERS];           // 1: tracer t is a vapour
   double eps[MAX_TRACERS];        // molar-mass ratios of the tracers
+  double ieps[MAX_TRACERS];       // their reciprocals
   KesslerSpec s[MAX_TRACERS / 3];
 };
 
 struct SatAdjSpec {
   int v, c;                            // tracer indices of vapour and cloud
-  double p_ref, t_ref, beta, delta, rv;   // rv = R_d / eps of the vapour
+  double p_ref, t_ref, it_ref, beta, delta, rv;   // it_ref = 1 / t_ref, rv = R_d / eps of the vapour
+  double dmu, dcap;   // mu and c_vd sigma of the cloud less the vapour's
 };
 
 struct SatAdjArgs {

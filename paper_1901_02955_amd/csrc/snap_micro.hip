@@ -22,13 +22,52 @@ __device__ __forceinline__ void set_tracer(double (&c)[NV], int idx, double val)
   for (int t = 0; t < NV - 5; ++t) c[5 + t] = t == idx ? val : c[5 + t];
 }
 
-// Entry `idx` of a per-tracer parameter table in the kernel arguments, by
-// compare-and-select (a runtime index would copy the argument struct to scratch).
-__device__ __forceinline__ double tracer_of(const double (&tab)[MAX_TRACERS], int idx) {
-  double r = 0.0;
-#pragma unroll
-  for (int t = 0; t < MAX_TRACERS; ++t) r = t == idx ? tab[t] : r;
-  return r;
+// The kernels over single cells take 256 consecutive cells of a level per block
+// (the rows of a level follow one another, so that only a level's last wave is
+// not full: with a block per row, 160 cells leave a sixth of the lanes of its
+// waves idle and 96 a quarter).
+template <typename A>
+dim3 micro_grid(const A& a) {
+  return dim3((unsigned)((((long long)a.nx * a.ny + 255) / 256) * a.nz));
+}
+template <typename A>
+__device__ __forceinline__ bool micro_cell(const A& a, int& i, int& j, int& k) {
+  const unsigned plane = (unsigned)a.nx * a.ny, per = (plane + 255) / 256;
+  k = (int)(blockIdx.x / per);
+  const unsigned c = (blockIdx.x - (unsigned)k * per) * 256 + threadIdx.x;
+  j = (int)(c / (unsigned)a.nx);
+  i = (int)(c - (unsigned)j * a.nx);
+  return c < plane;
+}
+
+// 1 / d and n / d (id = rcp(d)) to the last place: the hardware estimate, two
+// Newton-Raphson steps, and for the quotient the residual's correction; for
+// finite, normal arguments and results. Both kernels of this file are bound by
+// double-precision arithmetic, and a compiled division (scaling, estimate,
+// refinement, fix-up of the special cases) takes about twice these
+// instructions, and all of them again for every quotient of one denominator.
+// With the blocks of micro_grid and the pairs kept in registers (single-precision
+// storage): saturation adjustment of 256 x 192 x 128 cells with two pairs 246 ->
+// 170 us (70 for the memory it touches), Kessler step of 160 x 144 x 96 with two
+// species 141 -> 85. Against an 80-bit solution the root-mean-square errors are
+// those of the divisions or smaller (two species, double precision: cloud after
+// the adjustment 2.3e-16 of the field against 2.5e-16, after a Kessler step of
+// 2 s 2.07e-16 against 2.15e-16).
+__device__ __forceinline__ double rcp(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
+}
+__device__ __forceinline__ double quot(double n, double d, double id) {
+  const double q = n * id;
+  return fma(fma(-d, q, n), id, q);
+}
+
+// Saturation vapour pressure p* at temperature temp (App. D) and t_ref / temp.
+template <typename S>
+__device__ __forceinline__ double saturation(const S& sp, double temp, double itemp, double& itt) {
+  itt = sp.t_ref * itemp;
+  return sp.p_ref * exp(sp.beta * (1.0 - itt) - sp.delta * log(quot(temp, sp.t_ref, sp.it_ref)));
 }
 
 // Backward-Euler step of (q_v, q_c, q_p) by the Newton iteration of Sec. 3 in
@@ -45,9 +84,9 @@ __device__ __forceinline__ void kessler_solve(const KesslerSpec& sp, double qs, 
     const double cond = sat ? sp.k1 * (xv - qs) : 0.0;
     const double evap = sat ? 0.0 : sp.k4 * xp * (qs - xv);
     const double conv = sp.k2 * xc + sp.k3 * xc * xp;
-    const double r0 = (-cond + evap) - (xv - x0v) / dt;
-    const double r1 = (cond - conv) - (xc - x0c) / dt;
-    const double r2 = (-evap + conv) - (xp - x0p) / dt;
+    const double r0 = (-cond + evap) - (xv - x0v) * idt;
+    const double r1 = (cond - conv) - (xc - x0c) * idt;
+    const double r2 = (-evap + conv) - (xp - x0p) * idt;
     // M = I/dt - dPhi/dX (row 0, column 1 is zero in both regimes)
     const double A = sp.k2 + sp.k3 * xp, B = sp.k3 * xc, ev = sp.k4 * (qs - xv);
     const double m00 = idt - (sat ? -sp.k1 : -sp.k4 * xp);
@@ -59,7 +98,7 @@ __device__ __forceinline__ void kessler_solve(const KesslerSpec& sp, double qs, 
     const double c10 = m10 * m22 - m12 * m20;
     const double c20 = m10 * m21 - m11 * m20;
     const double det = m00 * c00 + m02 * c20;
-    const double idet = 1.0 / det;
+    const double idet = rcp(det);
     const double d0 = (r0 * c00 + m02 * (r1 * m21 - m11 * r2)) * idet;
     const double d1 = (m00 * (r1 * m22 - m12 * r2) - r0 * c10 + m02 * (m10 * r2 - r1 * m20)) * idet;
     const double d2 = (m00 * (m11 * r2 - r1 * m21) + r0 * c20) * idet;
@@ -72,14 +111,12 @@ __device__ __forceinline__ void kessler_solve(const KesslerSpec& sp, double qs, 
 
 }  // namespace
 
-// grid: x over interior rows (nz ny), y over the interior row
+// grid: micro_grid
 template <typename T, int NT>
 __global__ void __launch_bounds__(256) k_kessler(T* __restrict__ q, KesslerArgs a) {
   constexpr int NV = 5 + NT;
-  const int i = blockIdx.y * 256 + threadIdx.x;
-  if (i >= a.nx) return;
-  const int row = blockIdx.x;
-  const int j = row % a.ny, k = row / a.ny;
+  int i, j, k;
+  if (!micro_cell(a, i, j, k)) return;
   const long long o = (long long)(k + NG) * a.sz + (long long)(j + a.gy) * a.sy + (i + NG);
   double c[NV], x[NV];
 #pragma unroll
@@ -95,19 +132,20 @@ __global__ void __launch_bounds__(256) k_kessler(T* __restrict__ q, KesslerArgs 
     double gas = c[0] - st;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-      if (a.vap[t]) gas = gas + c[5 + t] / a.eps[t];
+      if (a.vap[t]) gas = gas + quot(c[5 + t], a.eps[t], a.ieps[t]);
     temp = x[4] / (a.rd * gas);
   }
-  const double rho = c[0];
+  const double rho = c[0], irho = rcp(rho), itemp = rcp(temp);
 #pragma unroll
-  for (int s = 0; s < MAX_TRACERS / 3; ++s) {
+  for (int s = 0; s < NT / 3; ++s) {
     if (s >= a.nspecies) break;
     const KesslerSpec& sp = a.s[s];
     // saturation mixing ratio over the cloud (App. D): p* eps / (R_d T) / rho
-    const double tt = temp / sp.t_ref;
-    const double pstar = sp.p_ref * exp(sp.beta * (1.0 - 1.0 / tt) - sp.delta * log(tt));
-    const double qs = pstar * sp.eps / (a.rd * temp) / rho;
-    double xv = tracer(c, sp.v) / rho, xc = tracer(c, sp.c) / rho, xp = tracer(c, sp.p) / rho;
+    double itt;
+    const double pstar = saturation(sp, temp, itemp, itt);
+    const double qs = quot(quot(pstar * sp.eps, a.rd * temp, itemp * a.ird), rho, irho);
+    const double c0v = tracer(c, sp.v), c0c = tracer(c, sp.c), c0p = tracer(c, sp.p);
+    double xv = quot(c0v, rho, irho), xc = quot(c0c, rho, irho), xp = quot(c0p, rho, irho);
     kessler_solve(sp, qs, a.dt, a.max_iter, a.tol, xv, xc, xp);
     set_tracer(c, sp.v, rho * xv);
     set_tracer(c, sp.c, rho * xc);
@@ -166,18 +204,16 @@ __device__ __forceinline__ void kessler_solve_adj(const KesslerSpec& sp, double 
 
 // q: padded state at the start of the step (read only). qb: interior layout,
 // in: cotangent of the state after the step, out: that of the state before.
-// grid: x over interior rows (nz ny), y over the interior row
+// grid: micro_grid
 template <typename T, int NT>
 __global__ void __launch_bounds__(256) k_kessler_adj(const T* __restrict__ q, T* __restrict__ qb,
                                                      KesslerArgs a) {
   constexpr int NV = 5 + NT;
-  const int i = blockIdx.y * 256 + threadIdx.x;
-  if (i >= a.nx) return;
-  const int row = blockIdx.x;
-  const int j = row % a.ny, k = row / a.ny;
+  int i, j, k;
+  if (!micro_cell(a, i, j, k)) return;
   const long long o = (long long)(k + NG) * a.sz + (long long)(j + a.gy) * a.sy + (i + NG);
   const long long rv = (long long)a.nx * a.ny * a.nz;
-  const long long ro = (long long)row * a.nx + i;
+  const long long ro = ((long long)k * a.ny + j) * a.nx + i;
   double c[NV], x[NV], cb[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
@@ -195,17 +231,17 @@ __global__ void __launch_bounds__(256) k_kessler_adj(const T* __restrict__ q, T*
     gas = c[0] - st;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-      if (a.vap[t]) gas = gas + c[5 + t] / a.eps[t];
+      if (a.vap[t]) gas = gas + quot(c[5 + t], a.eps[t], a.ieps[t]);
     temp = x[4] / (a.rd * gas);
   }
-  const double rho = c[0], irho = 1.0 / rho;
+  const double rho = c[0], irho = rcp(rho), itemp = rcp(temp);
   // the species' tracers leave the step through X* only: their cotangents
   // restart from zero and gather the X^n path below
   double yb[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) yb[v] = cb[v];
 #pragma unroll
-  for (int s = 0; s < MAX_TRACERS / 3; ++s) {
+  for (int s = 0; s < NT / 3; ++s) {
     if (s >= a.nspecies) break;
     const KesslerSpec& sp = a.s[s];
     set_tracer(cb, sp.v, 0.0);
@@ -214,12 +250,12 @@ __global__ void __launch_bounds__(256) k_kessler_adj(const T* __restrict__ q, T*
   }
   double rhob = 0.0, tb = 0.0;
 #pragma unroll
-  for (int s = 0; s < MAX_TRACERS / 3; ++s) {
+  for (int s = 0; s < NT / 3; ++s) {
     if (s >= a.nspecies) break;
     const KesslerSpec& sp = a.s[s];
-    const double tt = temp / sp.t_ref;
-    const double pstar = sp.p_ref * exp(sp.beta * (1.0 - 1.0 / tt) - sp.delta * log(tt));
-    const double qs = pstar * sp.eps / (a.rd * temp) / rho;
+    double itt;
+    const double pstar = saturation(sp, temp, itemp, itt);
+    const double qs = quot(quot(pstar * sp.eps, a.rd * temp, itemp * a.ird), rho, irho);
     const double x0[3] = {tracer(c, sp.v) * irho, tracer(c, sp.c) * irho, tracer(c, sp.p) * irho};
     double xv = x0[0], xc = x0[1], xp = x0[2];
     kessler_solve(sp, qs, a.dt, a.max_iter, a.tol, xv, xc, xp);
@@ -235,7 +271,7 @@ __global__ void __launch_bounds__(256) k_kessler_adj(const T* __restrict__ q, T*
     set_tracer(cb, sp.p, tracer(cb, sp.p) + x0b[2] * irho);
     rhob -= (x0b[0] * x0[0] + x0b[1] * x0[1] + x0b[2] * x0[2]) * irho;
     // q* = p*(T) eps / (R_d T rho): d ln q* / dT = beta t_ref / T^2 - (delta + 1) / T
-    tb += qsb * qs * ((sp.beta * sp.t_ref / temp - sp.delta - 1.0) / temp);
+    tb += qsb * qs * ((sp.beta * itt - sp.delta - 1.0) * itemp);
     rhob -= qsb * qs * irho;
   }
   // T = p / (R_d gas), gas = rho - sum_t rho_t + sum_vapours rho_t / eps_t
@@ -284,41 +320,53 @@ __global__ void __launch_bounds__(256) k_kessler_adj(const T* __restrict__ q, T*
 // satadj_iterate adjusts the conserved values c of one cell in place, given
 // heat0 = E - K, and leaves chem = sum mu rho and cap = c_vd (rho_d + sum sigma
 // rho) of the adjusted composition.
+// The pairs' densities stay in registers for the whole iteration, T's
+// reciprocal serves every quotient by T, cap's those by cap.
 template <int NT>
 __device__ __forceinline__ void satadj_iterate(double (&c)[5 + NT], const SatAdjArgs& a,
                                                double heat0, double& chem, double& cap) {
-  for (int it = 0; it < a.max_iter; ++it) {
-    double moved = 0.0;
+  constexpr int NS = NT / 2;
+  double vap[NS], cld[NS];
 #pragma unroll
-    for (int s = 0; s < MAX_TRACERS / 2; ++s) {
+  for (int s = 0; s < NS; ++s) {
+    vap[s] = s < a.nspecies ? tracer(c, a.s[s].v) : 0.0;
+    cld[s] = s < a.nspecies ? tracer(c, a.s[s].c) : 0.0;
+  }
+  for (int it = 0; it < a.max_iter; ++it) {
+    bool moving = false;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
       if (s >= a.nspecies) break;
       const SatAdjSpec& sp = a.s[s];
-      double rv = tracer(c, sp.v), rc = tracer(c, sp.c);
+      const double rv = vap[s], rc = cld[s];
       const double tot = rv + rc;
       if (!(tot > 0.0)) continue;
-      const double temp = (heat0 - chem) / cap;
-      const double tt = temp / sp.t_ref;
-      const double lam = sp.beta / tt - sp.delta;          // d ln p* / d ln T
-      const double pstar = sp.p_ref * exp(sp.beta * (1.0 - 1.0 / tt) - sp.delta * log(tt));
+      const double icap = rcp(cap);
+      const double temp = quot(heat0 - chem, cap, icap), itemp = rcp(temp);
+      double itt;
+      const double pstar = saturation(sp, temp, itemp, itt);
       const double f = rv * sp.rv * temp - pstar;          // > 0: supersaturated
       if (rc <= 0.0 && f <= 0.0) continue;                  // no cloud and below saturation
+      const double lam = sp.beta * itt - sp.delta;         // d ln p* / d ln T
       // latent heating per unit mass condensed: dT/dx = -(dmu + T dcap) / cap
-      const double dmu = tracer_of(a.mu, sp.c) - tracer_of(a.mu, sp.v);
-      const double dcap = a.cvd * (tracer_of(a.sigma, sp.c) - tracer_of(a.sigma, sp.v));
-      const double dTdx = -(dmu + temp * dcap) / cap;
-      double fp = -sp.rv * temp + rv * sp.rv * dTdx - pstar * lam / temp * dTdx;
+      const double dTdx = -(sp.dmu + temp * sp.dcap) * icap;
+      double fp = -sp.rv * temp + rv * sp.rv * dTdx - pstar * lam * itemp * dTdx;
       if (!(fp < 0.0)) fp = -sp.rv * temp;                 // keep the step downhill
-      double x = -f / fp;
+      double x = quot(-f, fp, rcp(fp));
       x = fmin(fmax(x, -rc), rv);
-      rv -= x;
-      rc += x;
-      chem += x * dmu;
-      cap += x * dcap;
-      set_tracer(c, sp.v, rv);
-      set_tracer(c, sp.c, rc);
-      moved = fmax(moved, fabs(x) / tot);
+      vap[s] = rv - x;
+      cld[s] = rc + x;
+      chem += x * sp.dmu;
+      cap += x * sp.dcap;
+      moving |= fabs(x) > a.tol * tot;
     }
-    if (moved <= a.tol) break;
+    if (!moving) break;
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (s >= a.nspecies) break;
+    set_tracer(c, a.s[s].v, vap[s]);
+    set_tracer(c, a.s[s].c, cld[s]);
   }
 }
 
@@ -337,14 +385,12 @@ __device__ __forceinline__ double satadj_heat(const double (&c)[5 + NT], const S
   return c[4] - 0.5 * (c[1] * c[1] + c[2] * c[2] + c[3] * c[3]) / c[0];
 }
 
-// grid: x over interior rows (nz ny), y over the interior row
+// grid: micro_grid
 template <typename T, int NT>
 __global__ void __launch_bounds__(256) k_satadj(T* __restrict__ q, SatAdjArgs a) {
   constexpr int NV = 5 + NT;
-  const int i = blockIdx.y * 256 + threadIdx.x;
-  if (i >= a.nx) return;
-  const int row = blockIdx.x;
-  const int j = row % a.ny, k = row / a.ny;
+  int i, j, k;
+  if (!micro_cell(a, i, j, k)) return;
   const long long o = (long long)(k + NG) * a.sz + (long long)(j + a.gy) * a.sy + (i + NG);
   double c[NV];
 #pragma unroll
@@ -376,14 +422,12 @@ template <typename T, int NT>
 __global__ void __launch_bounds__(256) k_satadj_adj(const T* __restrict__ q, T* __restrict__ qb,
                                                     SatAdjArgs a) {
   constexpr int NV = 5 + NT;
-  constexpr int NS = MAX_TRACERS / 2;
-  const int i = blockIdx.y * 256 + threadIdx.x;
-  if (i >= a.nx) return;
-  const int row = blockIdx.x;
-  const int j = row % a.ny, k = row / a.ny;
+  constexpr int NS = NT / 2;
+  int i, j, k;
+  if (!micro_cell(a, i, j, k)) return;
   const long long o = (long long)(k + NG) * a.sz + (long long)(j + a.gy) * a.sy + (i + NG);
   const long long rv = (long long)a.nx * a.ny * a.nz;
-  const long long ro = (long long)row * a.nx + i;
+  const long long ro = ((long long)k * a.ny + j) * a.nx + i;
   double c[NV], cf[NV], cb[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
@@ -402,13 +446,11 @@ __global__ void __launch_bounds__(256) k_satadj_adj(const T* __restrict__ q, T* 
     if (s >= a.nspecies) break;
     const SatAdjSpec& sp = a.s[s];
     xb[s] = tracer(cb, sp.c) - tracer(cb, sp.v);
-    const double dmu = tracer_of(a.mu, sp.c) - tracer_of(a.mu, sp.v);
-    const double dcap = a.cvd * (tracer_of(a.sigma, sp.c) - tracer_of(a.sigma, sp.v));
-    ts[s] = -(dmu + temp * dcap) / cap;
+    ts[s] = -(sp.dmu + temp * sp.dcap) / cap;
     if (tracer(cf, sp.c) > 0.0) {
-      const double tt = temp / sp.t_ref;
-      const double lam = sp.beta / tt - sp.delta;
-      const double pstar = sp.p_ref * exp(sp.beta * (1.0 - 1.0 / tt) - sp.delta * log(tt));
+      double itt;
+      const double pstar = saturation(sp, temp, 1.0 / temp, itt);
+      const double lam = sp.beta * itt - sp.delta;
       const double as = sp.rv * temp;
       const double gs = tracer(cf, sp.v) * sp.rv - pstar * lam / temp;
       num += gs * xb[s] / as;
@@ -533,7 +575,7 @@ int launch_sediment(int dtype, int ntracer, const StageArgs& a, hipStream_t st) 
 
 template <typename T>
 int launch_kessler_t(int ntracer, T* q, const KesslerArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.ny * a.nz), (unsigned)((a.nx + 255) / 256));
+  const dim3 grid = micro_grid(a);
   switch (ntracer) {
 #define SNAP_KESSLER_CASE(N)                                                        \
   case N:                                                                           \
@@ -558,7 +600,7 @@ int launch_kessler(int dtype, int ntracer, void* q, const KesslerArgs& a, hipStr
 
 template <typename T>
 int launch_kessler_adj_t(int ntracer, const T* q, T* qb, const KesslerArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.ny * a.nz), (unsigned)((a.nx + 255) / 256));
+  const dim3 grid = micro_grid(a);
   switch (ntracer) {
 #define SNAP_KESSLER_ADJ_CASE(N)                                                    \
   case N:                                                                           \
@@ -586,7 +628,7 @@ int launch_kessler_adj(int dtype, int ntracer, const void* q, void* qb, const Ke
 
 template <typename T>
 int launch_satadj_t(int ntracer, T* q, const SatAdjArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.ny * a.nz), (unsigned)((a.nx + 255) / 256));
+  const dim3 grid = micro_grid(a);
   switch (ntracer) {
 #define SNAP_SATADJ_CASE(N)                                                         \
   case N:                                                                           \
@@ -612,7 +654,7 @@ int launch_satadj(int dtype, int ntracer, void* q, const SatAdjArgs& a, hipStrea
 
 template <typename T>
 int launch_satadj_adj_t(int ntracer, const T* q, T* qb, const SatAdjArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.ny * a.nz), (unsigned)((a.nx + 255) / 256));
+  const dim3 grid = micro_grid(a);
   switch (ntracer) {
 #define SNAP_SATADJ_ADJ_CASE(N)                                                     \
   case N:                                                                           \
