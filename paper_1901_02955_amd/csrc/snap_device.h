@@ -373,6 +373,42 @@ __device__ __forceinline__ void lmars_flux(const T (&xl)[NV], const T (&xr)[NV],
   f[nrm] += pstar2;
 }
 
+// lmars_flux up to the upwind side: of the face states only rho', the normal
+// velocity and p' (index 0, 1, 2 of xl, xr) of both sides enter the interface
+// pressure and velocity; the tangential velocities and tracers of the other side
+// are not needed, and lmars_rest takes the upwind side's. Both as lmars_flux.
+template <typename T>
+struct LmarsFace {
+  T pstar2, ustar2, rs, ps, us;
+  bool left;
+};
+template <typename T>
+__device__ __forceinline__ LmarsFace<T> lmars_side(const T (&xl)[3], const T (&xr)[3], T rref,
+                                                   T pref, T gamma) {
+  LmarsFace<T> o;
+  const T rl = rref + xl[0], rr = rref + xr[0];
+  const T pl = pref + xl[2], pr = pref + xr[2];
+  const T RC = (rl + rr) * (sound_speed(gamma * pl, rl) + sound_speed(gamma * pr, rr));
+  o.pstar2 = fma(T(-0.25) * RC, xr[1] - xl[1], xl[2] + xr[2]);
+  o.ustar2 = fma(T(-4) * (xr[2] - xl[2]), rcp_fast(RC), xl[1] + xr[1]);
+  o.left = o.ustar2 > T(0);
+  o.rs = o.left ? rl : rr;
+  o.ps = o.left ? pl : pr;
+  o.us = o.left ? xl[1] : xr[1];
+  return o;
+}
+// f: mass, normal momentum, the two tangential momenta (t1, t2), energy.
+template <typename T>
+__device__ __forceinline__ void lmars_rest(const LmarsFace<T>& o, T t1, T t2, T gamma, T inv_gm1,
+                                           T (&f)[5]) {
+  const T H = fma(o.ps, gamma * inv_gm1, T(0.5) * o.rs * (o.us * o.us + t1 * t1 + t2 * t2));
+  f[0] = o.ustar2 * o.rs;
+  f[1] = fma(f[0], o.us, o.pstar2);
+  f[2] = f[0] * t1;
+  f[3] = f[0] * t2;
+  f[4] = o.ustar2 * H;
+}
+
 // HLLC flux at one face (the Riemann solver the paper compares LMARS with):
 // Davis outer wave speeds S_L = min(u_L - c_L, u_R - c_R), S_R = max(u_L + c_L,
 // u_R + c_R); contact speed S* = (p_R - p_L + d_L u_L - d_R u_R) / (d_L - d_R)

@@ -255,6 +255,23 @@ constexpr int two_sided() {
   return MIX || (D3 && sizeof(T) == 4 && NV == 6) ? NV : 5;
 }
 
+// The 3-D kernels that reconstruct the tangential velocities, too, on the upwind
+// side of a face only: LMARS with passive tracers in double precision, unpacked
+// item addresses. The interface velocity takes rho', the normal velocity and p'
+// of both sides, so those three are reconstructed per cell, and the two others
+// per face once its side is known: two of five two-sided reconstructions become
+// one-sided, for five more reads of the plane (registers selected in z) per
+// face. 256 x 256 x 128, four steps: 6365 -> 6156 us; 75 x 60 x 40 129 -> 126;
+// one to eight tracers on 256 x 192 x 96 within 0 to 1.5 %. Single precision,
+// at the edge of three waves per SIMD (155 -> 167 registers), took 2301 -> 2817
+// us (250 x 187 x 101, four steps), and the 2-D kernels, where every wave is
+// waited for, 718 -> 735 (256 x 256, twenty steps): they keep both sides, as do
+// HLLC and the mixture.
+template <typename T, int ND, bool MIX, bool HLLC, bool PACK>
+constexpr bool upwind_tangential() {
+  return sizeof(T) == 8 && ND == 5 && !MIX && !HLLC && !PACK;
+}
+
 // Output of one interior cell: either R itself or the stage combination (the
 // new state is left in R).
 template <typename T, int NV>
@@ -392,8 +409,9 @@ constexpr bool reconstruct_prefetch() {
 // variables while the others wait at the barrier. Without SPLIT they are a
 // last round of whole items, which needs fewer registers: the callers keep
 // that form where the split would cost a wave per SIMD or add spills.
-// ND: the variables reconstructed (the first ND of NV, two_sided).
-template <typename T, int NV, int ND, int TX, int TY, bool SPLIT = true>
+// ND: the variables reconstructed (the first ND of NV, two_sided; TAN: three of
+// them, upwind_tangential).
+template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool TAN, bool SPLIT = true>
 __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
                                                   bool linear,
                                                   T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
@@ -402,6 +420,8 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
   constexpr int PV = (TY + 6) * (TX + 6);   // plane stride between variables
   constexpr int FXV = TY * (TX + 1), FYV = (TY + 1) * TX;
   constexpr int NSP = I::NR - I::RREG * I::NTHR;   // cells left after the RREG rounds
+  // plane of the m-th reconstructed variable (TAN: rho', the normal velocity, p')
+  auto plane = [](int m, bool xa) { return !TAN ? m : (m == 0 ? 0 : (m == 1 ? (xa ? 1 : SNRM) : 4)); };
   if constexpr (SPLIT && NSP > 0) {
     constexpr int NSUB = NSP * ND;
     const int t0 = item_thread<I::NTHR>();
@@ -414,7 +434,7 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
       int ii, jj;
       if (sub < NSUB && plane_item<TX, TY>(it, w, h, xa, ii, jj)) {
         const int st = xa ? 1 : TX + 6;
-        const T* src = (xa ? &S.P[0][jj + 3][ii + 1] : &S.P[0][jj + 1][ii + 3]) + v * PV;
+        const T* src = (xa ? &S.P[0][jj + 3][ii + 1] : &S.P[0][jj + 1][ii + 3]) + plane(v, xa) * PV;
         T cur[5];
 #pragma unroll
         for (int mm = 0; mm < 5; ++mm) cur[mm] = src[mm * st];
@@ -454,11 +474,11 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
         if constexpr (RPF) {
           if (v + 1 < ND) {
 #pragma unroll
-            for (int m = 0; m < 5; ++m) nxt[m] = src[(v + 1) * PV + m * st];
+            for (int m = 0; m < 5; ++m) nxt[m] = src[plane(v + 1, xa) * PV + m * st];
           }
         } else {
 #pragma unroll
-          for (int m = 0; m < 5; ++m) cur[m] = src[v * PV + m * st];
+          for (int m = 0; m < 5; ++m) cur[m] = src[plane(v, xa) * PV + m * st];
         }
         T qm;
         weno5_cell<T>(cur[0], cur[1], cur[2], cur[3], cur[4], eps, linear, qm, qp[v]);
@@ -510,12 +530,12 @@ struct UpwindStencil {
 // two-sided reconstruction of every cell it saves a fifth of the WENO
 // instructions, the face states' way through LDS and the right states'
 // registers.
-template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool MIX, bool HLLC,
+template <typename T, int NV, int ND, int N2, int TX, int TY, int SNRM, bool MIX, bool HLLC,
           typename XRef, typename SRef>
 __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
                                             bool linear, T gamma, T inv_gm1, T gm1,
                                             const Mixture& mx, XRef xref, SRef sref,
-                                            const T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
+                                            const T (&QP)[PlaneItems<TX, TY>::RREG][N2]) {
   using I = PlaneItems<TX, TY>;
 #pragma unroll
   for (int r = 0; r < I::ROUNDS; ++r) {
@@ -523,37 +543,69 @@ __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int 
     bool xa;
     int ii, jj;
     if (it < I::NR && plane_item<TX, TY>(it, w, h, xa, ii, jj) && ii >= 0 && jj >= 0) {
-      T xl[ND], xr[ND], f[ND];
+      T xl[N2], xr[N2];
 #pragma unroll
-      for (int v = 0; v < ND; ++v) {
+      for (int v = 0; v < N2; ++v) {
         xr[v] = r < I::RREG ? QP[r < I::RREG ? r : 0][v] : S.QS[it - I::RREG * I::NTHR][v];
         xl[v] = xa ? S.FX[v][jj][ii] : S.FY[v][jj][ii];
       }
       T rr, pr;
-      bool left = false;
-      if (xa) {
-        xref(jj, rr, pr);
-        riemann_flux<T, ND, MIX, HLLC>(xl, xr, 1, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
-      } else {
-        sref(jj, rr, pr);
-        riemann_flux<T, ND, MIX, HLLC>(xl, xr, SNRM, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
-      }
-#pragma unroll
-      for (int v = 0; v < ND; ++v) {
+      if constexpr (N2 < ND) {   // upwind_tangential
         if (xa)
-          S.FX[v][jj][ii] = f[v];
+          xref(jj, rr, pr);
         else
-          S.FY[v][jj][ii] = f[v];
-      }
-      if (ND < NV && r < I::RREG) {
-        T* dst = xa ? &S.FX[ND][jj][ii] : &S.FY[ND][jj][ii];
+          sref(jj, rr, pr);
+        constexpr int PV = (TY + 6) * (TX + 6);
+        T* dst = xa ? &S.FX[0][jj][ii] : &S.FY[0][jj][ii];
         const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
+        const LmarsFace<T> o = lmars_side<T>(xl, xr, rr, pr, gamma);
         const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
-                                 left);
+                                 o.left);
+        const int n = xa ? 1 : SNRM, t1 = xa ? 2 : 1, t2 = xa ? 3 : 5 - SNRM;
+        const T q1 = u.face(t1 * PV, eps, linear);
+        SNAP_VAR_FENCE();
+        const T q2 = u.face(t2 * PV, eps, linear);
+        T f[5];
+        lmars_rest<T>(o, q1, q2, gamma, inv_gm1, f);
+        dst[0] = f[0];
+        dst[n * dv] = f[1];
+        dst[t1 * dv] = f[2];
+        dst[t2 * dv] = f[3];
+        dst[4 * dv] = f[4];
+        if (ND < NV && r < I::RREG) {
 #pragma unroll
-        for (int v = ND; v < NV; ++v) {
-          dst[(v - ND) * dv] = f[0] * u.face(v * (TY + 6) * (TX + 6), eps, linear);
-          SNAP_VAR_FENCE();
+          for (int v = ND; v < NV; ++v) {
+            dst[v * dv] = f[0] * u.face(v * PV, eps, linear);
+            SNAP_VAR_FENCE();
+          }
+        }
+      } else {
+        T f[ND];
+        bool left = false;
+        if (xa) {
+          xref(jj, rr, pr);
+          riemann_flux<T, ND, MIX, HLLC>(xl, xr, 1, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
+        } else {
+          sref(jj, rr, pr);
+          riemann_flux<T, ND, MIX, HLLC>(xl, xr, SNRM, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
+        }
+#pragma unroll
+        for (int v = 0; v < ND; ++v) {
+          if (xa)
+            S.FX[v][jj][ii] = f[v];
+          else
+            S.FY[v][jj][ii] = f[v];
+        }
+        if (ND < NV && r < I::RREG) {
+          T* dst = xa ? &S.FX[ND][jj][ii] : &S.FY[ND][jj][ii];
+          const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
+          const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
+                                   left);
+#pragma unroll
+          for (int v = ND; v < NV; ++v) {
+            dst[(v - ND) * dv] = f[0] * u.face(v * (TY + 6) * (TX + 6), eps, linear);
+            SNAP_VAR_FENCE();
+          }
         }
       }
     }
@@ -969,8 +1021,11 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
   };
 
   constexpr int ND = two_sided<T, NV, MIX, true>();
+  constexpr bool PACK = Stage3DShape<T, NT, MIX, SED, LOW>::pack;
+  constexpr bool TAN = upwind_tangential<T, ND, MIX, HLLC, PACK>();
+  constexpr int N2 = TAN ? 3 : ND;
   T W[5][NV];     // primitives of levels s-1 .. s+3 (own column)
-  // left states at the vertical face above the current level; for the tracers
+  // left states at the vertical face above the current level; for the variables
   // that are reconstructed on the upwind side only, their values on level s-2
   T qmc[NV];
   T fzc[NV];      // vertical flux at the lower face of the current level
@@ -1009,8 +1064,7 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
     }
   };
 
-  T QP[I::RREG][ND];
-  constexpr bool PACK = Stage3DShape<T, NT, MIX, SED, LOW>::pack;
+  T QP[I::RREG][N2];
   const ItemCodes<PACK ? NV : 1, PACK ? TX : 16, PACK ? TY : 16> IC(w, h);
   for (int s = k0 - 2; s < k1; ++s) {
     T wc[NV], qsc[NV], qnc[NV];
@@ -1053,8 +1107,8 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
       if constexpr (PACK)
         packed_reconstruct<T, NV, ND, TX, TY>(S, IC, eps, linear, QP);
       else
-        phase_reconstruct<T, NV, ND, TX, TY, split_reconstruct<T, NT, MIX, SED>()>(S, w, h, eps,
-                                                                                  linear, QP);
+        phase_reconstruct<T, NV, N2, TX, TY, 2, TAN, split_reconstruct<T, NT, MIX, SED>()>(
+            S, w, h, eps, linear, QP);
       __syncthreads();
       // ---- (L) LMARS at x and y faces (level references) ---------------------
       const T rbT = static_cast<T>(rbs), pbT = static_cast<T>(pbs);
@@ -1068,7 +1122,7 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
         __syncthreads();
         packed_tracer_rest<T, NV, ND, TX, TY>(S, IC, eps, linear);
       } else {
-        phase_lmars<T, NV, ND, TX, TY, 2, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t,
+        phase_lmars<T, NV, ND, N2, TX, TY, 2, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t,
                                                      a.mix, levref, levref, QP);
         __syncthreads();
         phase_tracer_rest<T, NV, ND, TX, TY>(S, w, h, eps, linear);
@@ -1084,18 +1138,41 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
       T qmn[ND], qpn[ND];
 #pragma unroll
       for (int v = 0; v < ND; ++v) {
+        if (TAN && (v == 1 || v == 2)) continue;
         weno5_cell<T>(W[0][v], W[1][v], W[2][v], W[3][v], W[4][v], eps, linear, qmn[v], qpn[v]);
         SNAP_VAR_FENCE();
       }
       if (s >= k0 - 1) {
         T fz[ND];
         bool left = false;
-        T xl[ND];
+        auto upwind = [&](int v) {   // levels s-2 .. s+2 up, or s+3 .. s-1 down
+          return weno5_face<T>(left ? qmc[v] : W[4][v], left ? W[0][v] : W[3][v],
+                               left ? W[1][v] : W[2][v], left ? W[2][v] : W[1][v],
+                               left ? W[3][v] : W[0][v], eps, linear);
+        };
+        if constexpr (TAN) {
+          const T xl[3] = {qmc[0], qmc[3], qmc[4]}, xr[3] = {qpn[0], qpn[3], qpn[4]};
+          const LmarsFace<T> o = lmars_side<T>(xl, xr, static_cast<T>(a.rbar_f[s + 1]),
+                                               static_cast<T>(a.pbar_f[s + 1]), gamma);
+          left = o.left;
+          const T q1 = upwind(1);
+          SNAP_VAR_FENCE();
+          const T q2 = upwind(2);
+          T f[5];
+          lmars_rest<T>(o, q1, q2, gamma, inv_gm1, f);
+          fz[0] = f[0];
+          fz[1] = f[2];
+          fz[2] = f[3];
+          fz[3] = f[1];
+          fz[4] = f[4];
+        } else {
+          T xl[ND];
 #pragma unroll
-        for (int v = 0; v < ND; ++v) xl[v] = qmc[v];
-        riemann_flux<T, ND, MIX, HLLC>(xl, qpn, 3, static_cast<T>(a.rbar_f[s + 1]),
-                                       static_cast<T>(a.pbar_f[s + 1]), gamma, inv_gm1, gm1t,
-                                       a.mix, fz, left);
+          for (int v = 0; v < ND; ++v) xl[v] = qmc[v];
+          riemann_flux<T, ND, MIX, HLLC>(xl, qpn, 3, static_cast<T>(a.rbar_f[s + 1]),
+                                         static_cast<T>(a.pbar_f[s + 1]), gamma, inv_gm1, gm1t,
+                                         a.mix, fz, left);
+        }
 #pragma unroll
         for (int v = 0; v < ND; ++v) {
           dfz[v] = fz[v] - fzc[v];
@@ -1104,17 +1181,14 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
         // tracers: the upwind side's value (levels s-2 .. s+2 up, or s+3 .. s-1 down)
 #pragma unroll
         for (int v = ND; v < NV; ++v) {
-          const T q = weno5_face<T>(left ? qmc[v] : W[4][v], left ? W[0][v] : W[3][v],
-                                    left ? W[1][v] : W[2][v], left ? W[2][v] : W[1][v],
-                                    left ? W[3][v] : W[0][v], eps, linear);
-          const T fq = fz[0] * q;
+          const T fq = fz[0] * upwind(v);
           dfz[v] = fq - fzc[v];
           fzc[v] = fq;
           SNAP_VAR_FENCE();
         }
       }
 #pragma unroll
-      for (int v = 0; v < ND; ++v) qmc[v] = qmn[v];
+      for (int v = 0; v < ND; ++v) qmc[v] = TAN && (v == 1 || v == 2) ? W[0][v] : qmn[v];
 #pragma unroll
       for (int v = ND; v < NV; ++v) qmc[v] = W[0][v];
     }
@@ -1265,7 +1339,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
   __syncthreads();
   constexpr int ND = two_sided<T, NV, MIX, false>();
   T QP[I::RREG][ND];
-  phase_reconstruct<T, NV, ND, TX, TZ>(S, w, h, eps, linear, QP);
+  phase_reconstruct<T, NV, ND, TX, TZ, 3, false>(S, w, h, eps, linear, QP);
   __syncthreads();
   auto xref = [&](int kk, T& r, T& p) {
     r = static_cast<T>(a.rbar_c[k0 + kk + NG]);
@@ -1275,7 +1349,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
     r = static_cast<T>(a.rbar_f[k0 + fk]);
     p = static_cast<T>(a.pbar_f[k0 + fk]);
   };
-  phase_lmars<T, NV, ND, TX, TZ, 3, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t, a.mix,
+  phase_lmars<T, NV, ND, ND, TX, TZ, 3, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t, a.mix,
                                                xref, zref, QP);
   __syncthreads();
   if constexpr (ND < NV) {
