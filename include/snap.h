@@ -26,9 +26,9 @@
  *
  * Ghost layers of q are library scratch: a call that reads q either fills them
  * from the interior according to `bc` or reads each ghost value at the
- * interior cell it copies (the 3-D time-stepping calls without tracers), and
- * leaves them unspecified. Interior cells of q are read-only except in the
- * time-stepping and microphysics calls.
+ * interior cell it copies (the time-stepping calls in 2-D, and in 3-D without
+ * tracers), and leaves them unspecified. Interior cells of q are read-only
+ * except in the time-stepping and microphysics calls.
  *
  * Calls are asynchronous on `stream` (a hipStream_t, NULL = default stream),
  * except snap_cfl_dt, snap_conservation_sums(_noalloc) and

@@ -409,9 +409,8 @@ constexpr bool reconstruct_prefetch() {
 // variables while the others wait at the barrier. Without SPLIT they are a
 // last round of whole items, which needs fewer registers: the callers keep
 // that form where the split would cost a wave per SIMD or add spills.
-// ND: the variables reconstructed (the first ND of NV, two_sided; TAN: three of
-// them, upwind_tangential).
-template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool TAN, bool SPLIT = true>
+// ND: the variables reconstructed (the first ND of NV, two_sided).
+template <typename T, int NV, int ND, int TX, int TY, bool SPLIT = true>
 __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
                                                   bool linear,
                                                   T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
@@ -420,8 +419,6 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
   constexpr int PV = (TY + 6) * (TX + 6);   // plane stride between variables
   constexpr int FXV = TY * (TX + 1), FYV = (TY + 1) * TX;
   constexpr int NSP = I::NR - I::RREG * I::NTHR;   // cells left after the RREG rounds
-  // plane of the m-th reconstructed variable (TAN: rho', the normal velocity, p')
-  auto plane = [](int m, bool xa) { return !TAN ? m : (m == 0 ? 0 : (m == 1 ? (xa ? 1 : SNRM) : 4)); };
   if constexpr (SPLIT && NSP > 0) {
     constexpr int NSUB = NSP * ND;
     const int t0 = item_thread<I::NTHR>();
@@ -434,7 +431,7 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
       int ii, jj;
       if (sub < NSUB && plane_item<TX, TY>(it, w, h, xa, ii, jj)) {
         const int st = xa ? 1 : TX + 6;
-        const T* src = (xa ? &S.P[0][jj + 3][ii + 1] : &S.P[0][jj + 1][ii + 3]) + plane(v, xa) * PV;
+        const T* src = (xa ? &S.P[0][jj + 3][ii + 1] : &S.P[0][jj + 1][ii + 3]) + v * PV;
         T cur[5];
 #pragma unroll
         for (int mm = 0; mm < 5; ++mm) cur[mm] = src[mm * st];
@@ -474,11 +471,11 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
         if constexpr (RPF) {
           if (v + 1 < ND) {
 #pragma unroll
-            for (int m = 0; m < 5; ++m) nxt[m] = src[plane(v + 1, xa) * PV + m * st];
+            for (int m = 0; m < 5; ++m) nxt[m] = src[(v + 1) * PV + m * st];
           }
         } else {
 #pragma unroll
-          for (int m = 0; m < 5; ++m) cur[m] = src[plane(v, xa) * PV + m * st];
+          for (int m = 0; m < 5; ++m) cur[m] = src[v * PV + m * st];
         }
         T qm;
         weno5_cell<T>(cur[0], cur[1], cur[2], cur[3], cur[4], eps, linear, qm, qp[v]);
@@ -530,12 +527,12 @@ struct UpwindStencil {
 // two-sided reconstruction of every cell it saves a fifth of the WENO
 // instructions, the face states' way through LDS and the right states'
 // registers.
-template <typename T, int NV, int ND, int N2, int TX, int TY, int SNRM, bool MIX, bool HLLC,
+template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool MIX, bool HLLC,
           typename XRef, typename SRef>
 __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
                                             bool linear, T gamma, T inv_gm1, T gm1,
                                             const Mixture& mx, XRef xref, SRef sref,
-                                            const T (&QP)[PlaneItems<TX, TY>::RREG][N2]) {
+                                            const T (&QP)[PlaneItems<TX, TY>::RREG][ND]) {
   using I = PlaneItems<TX, TY>;
 #pragma unroll
   for (int r = 0; r < I::ROUNDS; ++r) {
@@ -543,80 +540,177 @@ __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int 
     bool xa;
     int ii, jj;
     if (it < I::NR && plane_item<TX, TY>(it, w, h, xa, ii, jj) && ii >= 0 && jj >= 0) {
-      T xl[N2], xr[N2];
+      T xl[ND], xr[ND], f[ND];
 #pragma unroll
-      for (int v = 0; v < N2; ++v) {
+      for (int v = 0; v < ND; ++v) {
         xr[v] = r < I::RREG ? QP[r < I::RREG ? r : 0][v] : S.QS[it - I::RREG * I::NTHR][v];
         xl[v] = xa ? S.FX[v][jj][ii] : S.FY[v][jj][ii];
       }
       T rr, pr;
-      if constexpr (N2 < ND) {   // upwind_tangential
+      bool left = false;
+      // 2-D: the face's references are loaded ahead of the branch, both axes in one
+      // go (64 x 64, double precision, 20 steps: 547 -> 540 us; 256 x 256 724 ->
+      // 708). Not HLLC, whose instances of other tile shapes then contract
+      // differently: 1.8e-6 apart in single precision
+      constexpr bool REF = SNRM == 3 && !HLLC && !MIX;
+      if constexpr (REF) {
         if (xa)
           xref(jj, rr, pr);
         else
           sref(jj, rr, pr);
-        constexpr int PV = (TY + 6) * (TX + 6);
-        T* dst = xa ? &S.FX[0][jj][ii] : &S.FY[0][jj][ii];
-        const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
-        const LmarsFace<T> o = lmars_side<T>(xl, xr, rr, pr, gamma);
-        const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
-                                 o.left);
-        const int n = xa ? 1 : SNRM, t1 = xa ? 2 : 1, t2 = xa ? 3 : 5 - SNRM;
-        const T q1 = u.face(t1 * PV, eps, linear);
-        SNAP_VAR_FENCE();
-        const T q2 = u.face(t2 * PV, eps, linear);
-        T f[5];
-        lmars_rest<T>(o, q1, q2, gamma, inv_gm1, f);
-        dst[0] = f[0];
-        dst[n * dv] = f[1];
-        dst[t1 * dv] = f[2];
-        dst[t2 * dv] = f[3];
-        dst[4 * dv] = f[4];
-        if (ND < NV && r < I::RREG) {
-#pragma unroll
-          for (int v = ND; v < NV; ++v) {
-            dst[v * dv] = f[0] * u.face(v * PV, eps, linear);
-            SNAP_VAR_FENCE();
-          }
-        }
+      }
+      if (xa) {
+        if constexpr (!REF) xref(jj, rr, pr);
+        riemann_flux<T, ND, MIX, HLLC>(xl, xr, 1, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
       } else {
-        T f[ND];
-        bool left = false;
-        // 2-D: the face's references are loaded ahead of the branch, both axes in one
-        // go (64 x 64, double precision, 20 steps: 547 -> 540 us; 256 x 256 724 ->
-        // 708). Not HLLC, whose instances of other tile shapes then contract
-        // differently: 1.8e-6 apart in single precision
-        constexpr bool REF = SNRM == 3 && !HLLC;
-        if constexpr (REF) {
-          if (xa)
-            xref(jj, rr, pr);
-          else
-            sref(jj, rr, pr);
-        }
-        if (xa) {
-          if constexpr (!REF) xref(jj, rr, pr);
-          riemann_flux<T, ND, MIX, HLLC>(xl, xr, 1, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
-        } else {
-          if constexpr (!REF) sref(jj, rr, pr);
-          riemann_flux<T, ND, MIX, HLLC>(xl, xr, SNRM, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
-        }
+        if constexpr (!REF) sref(jj, rr, pr);
+        riemann_flux<T, ND, MIX, HLLC>(xl, xr, SNRM, rr, pr, gamma, inv_gm1, gm1, mx, f, left);
+      }
 #pragma unroll
-        for (int v = 0; v < ND; ++v) {
-          if (xa)
-            S.FX[v][jj][ii] = f[v];
-          else
-            S.FY[v][jj][ii] = f[v];
-        }
-        if (ND < NV && r < I::RREG) {
-          T* dst = xa ? &S.FX[ND][jj][ii] : &S.FY[ND][jj][ii];
-          const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
-          const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
-                                   left);
+      for (int v = 0; v < ND; ++v) {
+        if (xa)
+          S.FX[v][jj][ii] = f[v];
+        else
+          S.FY[v][jj][ii] = f[v];
+      }
+      if (ND < NV && r < I::RREG) {
+        T* dst = xa ? &S.FX[ND][jj][ii] : &S.FY[ND][jj][ii];
+        const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
+        const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
+                                 left);
 #pragma unroll
-          for (int v = ND; v < NV; ++v) {
-            dst[(v - ND) * dv] = f[0] * u.face(v * (TY + 6) * (TX + 6), eps, linear);
-            SNAP_VAR_FENCE();
-          }
+        for (int v = ND; v < NV; ++v) {
+          dst[(v - ND) * dv] = f[0] * u.face(v * (TY + 6) * (TX + 6), eps, linear);
+          SNAP_VAR_FENCE();
+        }
+      }
+    }
+  }
+}
+
+// Phases R and L of the kernels that reconstruct the tangential velocities on
+// the upwind side (upwind_tangential): three variables per cell item, then at a
+// face the two tangential velocities and the tracers from the plane.
+template <typename T, int NV, int TX, int TY, int SNRM>
+__device__ __forceinline__ void phase_reconstruct_sides(Plane<T, NV, TX, TY>& S, int w, int h,
+                                                        T eps, bool linear,
+                                                        T (&QP)[PlaneItems<TX, TY>::RREG][3]) {
+  using I = PlaneItems<TX, TY>;
+  constexpr int PV = (TY + 6) * (TX + 6);   // plane stride between variables
+  constexpr int FXV = TY * (TX + 1), FYV = (TY + 1) * TX;
+  constexpr int NSP = I::NR - I::RREG * I::NTHR;   // cells left after the RREG rounds
+  // plane of the m-th reconstructed variable: rho', the normal velocity, p'
+  auto plane = [](int m, bool xa) { return m == 0 ? 0 : (m == 1 ? (xa ? 1 : SNRM) : 4); };
+  if constexpr (NSP > 0) {
+    constexpr int NSUB = NSP * 3;
+    const int t0 = item_thread<I::NTHR>();
+#pragma unroll
+    for (int m = 0; m < (NSUB + I::NTHR - 1) / I::NTHR; ++m) {
+      const int sub = t0 + m * I::NTHR;
+      const int v = sub / NSP, c = sub - v * NSP;
+      const int it = I::RREG * I::NTHR + c;
+      bool xa;
+      int ii, jj;
+      if (sub < NSUB && plane_item<TX, TY>(it, w, h, xa, ii, jj)) {
+        const int st = xa ? 1 : TX + 6;
+        const T* src = (xa ? &S.P[0][jj + 3][ii + 1] : &S.P[0][jj + 1][ii + 3]) + plane(v, xa) * PV;
+        T cur[5];
+#pragma unroll
+        for (int mm = 0; mm < 5; ++mm) cur[mm] = src[mm * st];
+        T qm, qp;
+        weno5_cell<T>(cur[0], cur[1], cur[2], cur[3], cur[4], eps, linear, qm, qp);
+        if (xa ? ii < w : jj < h) {
+          if (xa)
+            S.FX[v][jj][ii + 1] = qm;
+          else
+            S.FY[v][jj + 1][ii] = qm;
+        }
+        S.QS[c][v] = qp;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < I::RREG; ++r) {
+    const int it = item_thread<I::NTHR>() + r * I::NTHR;
+    bool xa;
+    int ii, jj;
+    if (it < I::NR && plane_item<TX, TY>(it, w, h, xa, ii, jj)) {
+      const int st = xa ? 1 : TX + 6;
+      const T* src = xa ? &S.P[0][jj + 3][ii + 1] : &S.P[0][jj + 1][ii + 3];
+      T* dst = xa ? &S.FX[0][jj][ii + 1] : &S.FY[0][jj + 1][ii];
+      const int dv = xa ? FXV : FYV;
+      const bool put = xa ? ii < w : jj < h;
+      T qp[3];
+      T cur[5];
+#pragma unroll
+      for (int m = 0; m < 5; ++m) cur[m] = src[m * st];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        T nxt[5];
+        if (v + 1 < 3) {
+#pragma unroll
+          for (int m = 0; m < 5; ++m) nxt[m] = src[plane(v + 1, xa) * PV + m * st];
+        }
+        T qm;
+        weno5_cell<T>(cur[0], cur[1], cur[2], cur[3], cur[4], eps, linear, qm, qp[v]);
+        if (put) dst[v * dv] = qm;
+        SNAP_VAR_FENCE();
+        if (v + 1 < 3) {
+#pragma unroll
+          for (int m = 0; m < 5; ++m) cur[m] = nxt[m];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 3; ++v) QP[r][v] = qp[v];
+    }
+  }
+}
+
+template <typename T, int NV, int TX, int TY, int SNRM, typename XRef, typename SRef>
+__device__ __forceinline__ void phase_lmars_sides(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
+                                                  bool linear, T gamma, T inv_gm1, XRef xref,
+                                                  SRef sref,
+                                                  const T (&QP)[PlaneItems<TX, TY>::RREG][3]) {
+  using I = PlaneItems<TX, TY>;
+#pragma unroll
+  for (int r = 0; r < I::ROUNDS; ++r) {
+    const int it = item_thread<I::NTHR>() + r * I::NTHR;
+    bool xa;
+    int ii, jj;
+    if (it < I::NR && plane_item<TX, TY>(it, w, h, xa, ii, jj) && ii >= 0 && jj >= 0) {
+      T xl[3], xr[3];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        xr[v] = r < I::RREG ? QP[r < I::RREG ? r : 0][v] : S.QS[it - I::RREG * I::NTHR][v];
+        xl[v] = xa ? S.FX[v][jj][ii] : S.FY[v][jj][ii];
+      }
+      T rr, pr;
+      if (xa)
+        xref(jj, rr, pr);
+      else
+        sref(jj, rr, pr);
+      constexpr int PV = (TY + 6) * (TX + 6);
+      T* dst = xa ? &S.FX[0][jj][ii] : &S.FY[0][jj][ii];
+      const int dv = xa ? TY * (TX + 1) : (TY + 1) * TX;
+      const LmarsFace<T> o = lmars_side<T>(xl, xr, rr, pr, gamma);
+      const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
+                               o.left);
+      const int n = xa ? 1 : SNRM, t1 = xa ? 2 : 1, t2 = xa ? 3 : 5 - SNRM;
+      const T q1 = u.face(t1 * PV, eps, linear);
+      SNAP_VAR_FENCE();
+      const T q2 = u.face(t2 * PV, eps, linear);
+      T f[5];
+      lmars_rest<T>(o, q1, q2, gamma, inv_gm1, f);
+      dst[0] = f[0];
+      dst[n * dv] = f[1];
+      dst[t1 * dv] = f[2];
+      dst[t2 * dv] = f[3];
+      dst[4 * dv] = f[4];
+      if (NV > 5 && r < I::RREG) {
+#pragma unroll
+        for (int v = 5; v < NV; ++v) {
+          dst[v * dv] = f[0] * u.face(v * PV, eps, linear);
+          SNAP_VAR_FENCE();
         }
       }
     }
@@ -1117,9 +1211,11 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
       // ---- (R) WENO5 in x and y ---------------------------------------------
       if constexpr (PACK)
         packed_reconstruct<T, NV, ND, TX, TY>(S, IC, eps, linear, QP);
+      else if constexpr (TAN)
+        phase_reconstruct_sides<T, NV, TX, TY, 2>(S, w, h, eps, linear, QP);
       else
-        phase_reconstruct<T, NV, N2, TX, TY, 2, TAN, split_reconstruct<T, NT, MIX, SED>()>(
-            S, w, h, eps, linear, QP);
+        phase_reconstruct<T, NV, ND, TX, TY, split_reconstruct<T, NT, MIX, SED>()>(S, w, h, eps,
+                                                                                  linear, QP);
       __syncthreads();
       // ---- (L) LMARS at x and y faces (level references) ---------------------
       const T rbT = static_cast<T>(rbs), pbT = static_cast<T>(pbs);
@@ -1133,8 +1229,12 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
         __syncthreads();
         packed_tracer_rest<T, NV, ND, TX, TY>(S, IC, eps, linear);
       } else {
-        phase_lmars<T, NV, ND, N2, TX, TY, 2, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t,
-                                                     a.mix, levref, levref, QP);
+        if constexpr (TAN)
+          phase_lmars_sides<T, NV, TX, TY, 2>(S, w, h, eps, linear, gamma, inv_gm1, levref, levref,
+                                              QP);
+        else
+          phase_lmars<T, NV, ND, TX, TY, 2, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t,
+                                                       a.mix, levref, levref, QP);
         __syncthreads();
         phase_tracer_rest<T, NV, ND, TX, TY>(S, w, h, eps, linear);
       }
@@ -1146,22 +1246,22 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
       if (wzf) wc[3] = -wc[3];
       cons_to_prim_t<T, NV, MIX>(wc, level_ref(a.pert, a.rbar_c[s + 3 + NG], a.pbar_c[s + 3 + NG]),
                                  a.gm1, a.mix, W[4]);
-      T qmn[ND], qpn[ND];
+      if constexpr (TAN) {
+        T qmn[ND], qpn[ND];
 #pragma unroll
-      for (int v = 0; v < ND; ++v) {
-        if (TAN && (v == 1 || v == 2)) continue;
-        weno5_cell<T>(W[0][v], W[1][v], W[2][v], W[3][v], W[4][v], eps, linear, qmn[v], qpn[v]);
-        SNAP_VAR_FENCE();
-      }
-      if (s >= k0 - 1) {
-        T fz[ND];
-        bool left = false;
-        auto upwind = [&](int v) {   // levels s-2 .. s+2 up, or s+3 .. s-1 down
-          return weno5_face<T>(left ? qmc[v] : W[4][v], left ? W[0][v] : W[3][v],
-                               left ? W[1][v] : W[2][v], left ? W[2][v] : W[1][v],
-                               left ? W[3][v] : W[0][v], eps, linear);
-        };
-        if constexpr (TAN) {
+        for (int v = 0; v < ND; ++v) {
+          if (v == 1 || v == 2) continue;
+          weno5_cell<T>(W[0][v], W[1][v], W[2][v], W[3][v], W[4][v], eps, linear, qmn[v], qpn[v]);
+          SNAP_VAR_FENCE();
+        }
+        if (s >= k0 - 1) {
+          T fz[ND];
+          bool left;
+          auto upwind = [&](int v) {   // levels s-2 .. s+2 up, or s+3 .. s-1 down
+            return weno5_face<T>(left ? qmc[v] : W[4][v], left ? W[0][v] : W[3][v],
+                                 left ? W[1][v] : W[2][v], left ? W[2][v] : W[1][v],
+                                 left ? W[3][v] : W[0][v], eps, linear);
+          };
           const T xl[3] = {qmc[0], qmc[3], qmc[4]}, xr[3] = {qpn[0], qpn[3], qpn[4]};
           const LmarsFace<T> o = lmars_side<T>(xl, xr, static_cast<T>(a.rbar_f[s + 1]),
                                                static_cast<T>(a.pbar_f[s + 1]), gamma);
@@ -1176,32 +1276,62 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
           fz[2] = f[3];
           fz[3] = f[1];
           fz[4] = f[4];
-        } else {
+#pragma unroll
+          for (int v = 0; v < ND; ++v) {
+            dfz[v] = fz[v] - fzc[v];
+            fzc[v] = fz[v];
+          }
+          // tracers: the upwind side's value (levels s-2 .. s+2 up, or s+3 .. s-1 down)
+#pragma unroll
+          for (int v = ND; v < NV; ++v) {
+            const T fq = fz[0] * upwind(v);
+            dfz[v] = fq - fzc[v];
+            fzc[v] = fq;
+            SNAP_VAR_FENCE();
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < ND; ++v) qmc[v] = v == 1 || v == 2 ? W[0][v] : qmn[v];
+#pragma unroll
+        for (int v = ND; v < NV; ++v) qmc[v] = W[0][v];
+      } else {
+        T qmn[ND], qpn[ND];
+#pragma unroll
+        for (int v = 0; v < ND; ++v) {
+          weno5_cell<T>(W[0][v], W[1][v], W[2][v], W[3][v], W[4][v], eps, linear, qmn[v], qpn[v]);
+          SNAP_VAR_FENCE();
+        }
+        if (s >= k0 - 1) {
+          T fz[ND];
+          bool left = false;
           T xl[ND];
 #pragma unroll
           for (int v = 0; v < ND; ++v) xl[v] = qmc[v];
           riemann_flux<T, ND, MIX, HLLC>(xl, qpn, 3, static_cast<T>(a.rbar_f[s + 1]),
                                          static_cast<T>(a.pbar_f[s + 1]), gamma, inv_gm1, gm1t,
                                          a.mix, fz, left);
+#pragma unroll
+          for (int v = 0; v < ND; ++v) {
+            dfz[v] = fz[v] - fzc[v];
+            fzc[v] = fz[v];
+          }
+          // tracers: the upwind side's value (levels s-2 .. s+2 up, or s+3 .. s-1 down)
+#pragma unroll
+          for (int v = ND; v < NV; ++v) {
+            const T q = weno5_face<T>(left ? qmc[v] : W[4][v], left ? W[0][v] : W[3][v],
+                                      left ? W[1][v] : W[2][v], left ? W[2][v] : W[1][v],
+                                      left ? W[3][v] : W[0][v], eps, linear);
+            const T fq = fz[0] * q;
+            dfz[v] = fq - fzc[v];
+            fzc[v] = fq;
+            SNAP_VAR_FENCE();
+          }
         }
 #pragma unroll
-        for (int v = 0; v < ND; ++v) {
-          dfz[v] = fz[v] - fzc[v];
-          fzc[v] = fz[v];
-        }
-        // tracers: the upwind side's value (levels s-2 .. s+2 up, or s+3 .. s-1 down)
+        for (int v = 0; v < ND; ++v) qmc[v] = qmn[v];
 #pragma unroll
-        for (int v = ND; v < NV; ++v) {
-          const T fq = fz[0] * upwind(v);
-          dfz[v] = fq - fzc[v];
-          fzc[v] = fq;
-          SNAP_VAR_FENCE();
-        }
+        for (int v = ND; v < NV; ++v) qmc[v] = W[0][v];
       }
-#pragma unroll
-      for (int v = 0; v < ND; ++v) qmc[v] = TAN && (v == 1 || v == 2) ? W[0][v] : qmn[v];
-#pragma unroll
-      for (int v = ND; v < NV; ++v) qmc[v] = W[0][v];
     }
     // ---- (D) divergence, gravity, output -------------------------------------
     if (ND < NV && s >= k0) __syncthreads();   // the last tracer fluxes
@@ -1350,7 +1480,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
   __syncthreads();
   constexpr int ND = two_sided<T, NV, MIX, false>();
   T QP[I::RREG][ND];
-  phase_reconstruct<T, NV, ND, TX, TZ, 3, false>(S, w, h, eps, linear, QP);
+  phase_reconstruct<T, NV, ND, TX, TZ>(S, w, h, eps, linear, QP);
   __syncthreads();
   auto xref = [&](int kk, T& r, T& p) {
     r = static_cast<T>(a.rbar_c[k0 + kk + NG]);
@@ -1360,7 +1490,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
     r = static_cast<T>(a.rbar_f[k0 + fk]);
     p = static_cast<T>(a.pbar_f[k0 + fk]);
   };
-  phase_lmars<T, NV, ND, ND, TX, TZ, 3, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t, a.mix,
+  phase_lmars<T, NV, ND, TX, TZ, 3, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t, a.mix,
                                                xref, zref, QP);
   __syncthreads();
   if constexpr (ND < NV) {
