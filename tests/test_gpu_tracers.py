@@ -44,7 +44,8 @@ def test_every_count(nt, dtype):
     check(31, 1, 18, nt, dtype, (nt + 1) % 2, (nt % 2, 0, 1), linear=nt == 3)
 
 
-@pytest.mark.parametrize("dtype,nt", [(torch.float64, 3), (torch.float64, 4), (torch.float32, 5)],
-                         ids=["f64-3", "f64-4", "f32-5"])
+@pytest.mark.parametrize("dtype,nt", [(torch.float64, 3), (torch.float64, 4), (torch.float32, 2),
+                                      (torch.float32, 3), (torch.float32, 5)],
+                         ids=["f64-3", "f64-4", "f32-2", "f32-3", "f32-5"])
 def test_full_launch(dtype, nt):
     check(113, 97, 40, nt, dtype, 0, (0, 1, 1))
