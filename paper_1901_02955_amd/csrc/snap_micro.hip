@@ -25,19 +25,24 @@ __device__ __forceinline__ void set_tracer(double (&c)[NV], int idx, double val)
 // The kernels over single cells take 256 consecutive cells of a level per block
 // (the rows of a level follow one another, so that only a level's last wave is
 // not full: with a block per row, 160 cells leave a sixth of the lanes of its
-// waves idle and 96 a quarter).
+// waves idle and 96 a quarter). A launch holds fewer than 2^32 threads along x,
+// which a state of 2^32 cells and less can reach, and 65535 blocks along y and z:
+// the levels lie along y and, beyond LEVELS_Y of them, z.
+constexpr int LEVELS_Y = 32768;
 template <typename A>
 dim3 micro_grid(const A& a) {
-  return dim3((unsigned)((((long long)a.nx * a.ny + 255) / 256) * a.nz));
+  const int ly = a.nz < LEVELS_Y ? a.nz : LEVELS_Y;
+  return dim3((unsigned)(((long long)a.nx * a.ny + 255) / 256), (unsigned)ly,
+              (unsigned)((a.nz + ly - 1) / ly));
 }
 template <typename A>
 __device__ __forceinline__ bool micro_cell(const A& a, int& i, int& j, int& k) {
-  const unsigned plane = (unsigned)a.nx * a.ny, per = (plane + 255) / 256;
-  k = (int)(blockIdx.x / per);
-  const unsigned c = (blockIdx.x - (unsigned)k * per) * 256 + threadIdx.x;
+  const unsigned plane = (unsigned)a.nx * a.ny;   // below 2^32 for any state in memory
+  const unsigned c = blockIdx.x * 256 + threadIdx.x;
+  k = (int)(blockIdx.z * gridDim.y + blockIdx.y);
   j = (int)(c / (unsigned)a.nx);
   i = (int)(c - (unsigned)j * a.nx);
-  return c < plane;
+  return c < plane && k < a.nz;
 }
 
 // 1 / d and n / d (id = rcp(d)) to the last place: the hardware estimate, two
