@@ -584,6 +584,8 @@ __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int 
           SNAP_VAR_FENCE();
         }
       }
+      if (HLLC && ND < NV && r >= I::RREG)
+        S.QS[it - I::RREG * I::NTHR][0] = left ? T(1) : T(0);   // for phase_tracer_rest
     }
   }
 }
@@ -719,9 +721,12 @@ __device__ __forceinline__ void phase_lmars_sides(Plane<T, NV, TX, TY>& S, int w
 
 // The tracer fluxes of the faces beyond the RREG rounds (64 of the 544 of a
 // 16 x 16 tile), one (face, tracer) pair per thread and pass so that every wave
-// takes a share (a barrier after phase_lmars; the upwind side is the mass
-// flux's sign).
-template <typename T, int NV, int ND, int TX, int TY>
+// takes a share (a barrier after phase_lmars). The upwind side is the one the
+// flux took, or two tiles that share a face could carry different values through
+// it: the sign of the mass flux under LMARS, which forms it as a product with
+// the interface velocity; under HLLC, where it is a sum that rounding can leave
+// with either sign in still air, the side phase_lmars left in QS.
+template <typename T, int NV, int ND, int TX, int TY, bool HLLC>
 __device__ __forceinline__ void phase_tracer_rest(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
                                                   bool linear) {
   using I = PlaneItems<TX, TY>;
@@ -739,8 +744,9 @@ __device__ __forceinline__ void phase_tracer_rest(Plane<T, NV, TX, TY>& S, int w
           plane_item<TX, TY>(I::RREG * I::NTHR + sub % NSP, w, h, xa, ii, jj) && ii >= 0 &&
           jj >= 0) {
         const T f0 = xa ? S.FX[0][jj][ii] : S.FY[0][jj][ii];
+        const bool left = HLLC ? S.QS[sub % NSP][0] != T(0) : f0 > T(0);
         const UpwindStencil<T> u(xa ? &S.P[0][jj + 3][ii] : &S.P[0][jj][ii + 3], xa ? 1 : TX + 6,
-                                 f0 > T(0));
+                                 left);
         const T q = u.face(v * (TY + 6) * (TX + 6), eps, linear);
         (xa ? S.FX[v][jj][ii] : S.FY[v][jj][ii]) = f0 * q;
       }
@@ -903,12 +909,14 @@ __device__ __forceinline__ void packed_lmars(Plane<T, NV, TX, TY>& S,
           SNAP_VAR_FENCE();
         }
       }
+      if (HLLC && ND < NV && r == I::RREG)
+        S.QS[item_thread<I::NTHR>()][0] = left ? T(1) : T(0);   // for packed_tracer_rest
     }
   }
 }
 
 // As phase_tracer_rest.
-template <typename T, int NV, int ND, int TX, int TY>
+template <typename T, int NV, int ND, int TX, int TY, bool HLLC>
 __device__ __forceinline__ void packed_tracer_rest(Plane<T, NV, TX, TY>& S,
                                                    const ItemCodes<NV, TX, TY>& IC, T eps,
                                                    bool linear) {
@@ -923,7 +931,8 @@ __device__ __forceinline__ void packed_tracer_rest(Plane<T, NV, TX, TY>& S,
       T* fp = fb + C::dst(x) - C::face(x);
       const T f0 = fp[0];
       const int st = C::cell(x);
-      const UpwindStencil<T> u(base + C::src(x) - st, st, f0 > T(0));
+      const bool left = HLLC ? S.QS[item_thread<I::NTHR>() % C::NSP][0] != T(0) : f0 > T(0);
+      const UpwindStencil<T> u(base + C::src(x) - st, st, left);
 #pragma unroll
       for (int m = 0; m < (NSUB + I::NTHR - 1) / I::NTHR; ++m) {
         const int sub = item_thread<I::NTHR>() + m * I::NTHR, v = ND + sub / C::NSP;
@@ -1229,7 +1238,7 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
         packed_lmars<T, NV, ND, TX, TY, 2, MIX, HLLC>(S, IC, eps, linear, gamma, inv_gm1, gm1t,
                                                       a.mix, rbT, pbT, QP);
         __syncthreads();
-        packed_tracer_rest<T, NV, ND, TX, TY>(S, IC, eps, linear);
+        packed_tracer_rest<T, NV, ND, TX, TY, HLLC>(S, IC, eps, linear);
       } else {
         if constexpr (TAN)
           phase_lmars_sides<T, NV, TX, TY, 2>(S, w, h, eps, linear, gamma, inv_gm1, levref, levref,
@@ -1238,7 +1247,7 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
           phase_lmars<T, NV, ND, TX, TY, 2, MIX, HLLC>(S, w, h, eps, linear, gamma, inv_gm1, gm1t,
                                                        a.mix, levref, levref, QP);
         __syncthreads();
-        phase_tracer_rest<T, NV, ND, TX, TY>(S, w, h, eps, linear);
+        phase_tracer_rest<T, NV, ND, TX, TY, HLLC>(S, w, h, eps, linear);
       }
     }
     // ---- vertical direction, own column: face s+1/2 (z-face index s+1) -------
@@ -1496,7 +1505,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
                                                xref, zref, QP);
   __syncthreads();
   if constexpr (ND < NV) {
-    phase_tracer_rest<T, NV, ND, TX, TZ>(S, w, h, eps, linear);
+    phase_tracer_rest<T, NV, ND, TX, TZ, HLLC>(S, w, h, eps, linear);
     __syncthreads();
   }
   unsigned long long smx = 0ULL;
