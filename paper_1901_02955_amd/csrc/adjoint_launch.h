@@ -8,6 +8,14 @@
 
 namespace snap {
 
+// Blocks of up to 512 threads in rows of at most 2^22: a launch holds fewer than
+// 2^32 threads along an axis, which a wave per line passes from 2^26 short lines
+// on (8192 x 8192 x 2 in single precision: 27 GB for all arrays).
+inline dim3 lane_grid(long long blocks) {
+  const long long rows = (blocks + (1LL << 22) - 1) >> 22;
+  return dim3((unsigned)((blocks + rows - 1) / rows), (unsigned)rows);
+}
+
 template <typename T, int NV, int D, bool HLLC, bool MIX>
 void adj_lane_launch(const T* q, const T* r, const AdjArgs& a, T* P, const FoldOut<T>& fo,
                      hipStream_t st) {
@@ -15,8 +23,8 @@ void adj_lane_launch(const T* q, const T* r, const AdjArgs& a, T* P, const FoldO
   const int nseg = lane_segments(D == 0 ? a.nx : (D == 1 ? a.ny : a.nz));
   const long long groups = D == 0 ? ((long long)a.ny * a.nz + NW - 1) / NW
                                   : (long long)((a.nx + NW - 1) / NW) * (D == 1 ? a.nz : a.ny);
-  hipLaunchKernelGGL((k_adj_lane<T, NV, D, HLLC, MIX>), dim3((unsigned)(groups * nseg)),
-                     dim3(64 * NW), 0, st, q, r, a, nseg, P, fo);
+  hipLaunchKernelGGL((k_adj_lane<T, NV, D, HLLC, MIX>), lane_grid(groups * nseg), dim3(64 * NW),
+                     0, st, q, r, a, nseg, (int)groups, P, fo);
 }
 
 // The y and z directions march along their lines (k_adj_march) in single

@@ -739,9 +739,10 @@ __device__ __forceinline__ void fold_store(const FoldOut<T>& f, const T* __restr
 // fo: with fo.fold (z direction, after k_adj_xmerge) a cell at least 3 from the
 // y and z edges is complete here, and its conserved cotangent is formed and
 // stored instead of P (k_adj_consfold then takes the rows that are left).
-// Grid: the segments (lane_segments) of the positions -3 .. nd + 2, and in a
-// segment the line groups (x: lines (j, k), a line per wave; y, z: groups of
-// lane_waves lines, x fastest).
+// Blocks: the segments (lane_segments) of the positions -3 .. nd + 2, and in a
+// segment the ng line groups (x: lines (j, k), a line per wave; y, z: groups of
+// lane_waves lines, x fastest), numbered over a grid of one or more rows
+// (lane_grid); the last row's blocks beyond them have nothing to do.
 // 256 x 256 x 128, one gradient step in double precision (kept stages): 12.45 ms
 // with tiles of lines in LDS and five barriers per direction, 8.9 ms now; the
 // x direction of 101 x 84 x 64 66 -> 39 us, y 82 -> 55; seven variables on
@@ -776,7 +777,7 @@ __device__ __forceinline__ double lane_shift(double x, int addr) {
 
 template <typename T, int NV, int D, bool HLLC, bool MIX>
 __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
-    k_adj_lane(const T* __restrict__ q, const T* __restrict__ rb, AdjArgs a, int nseg,
+    k_adj_lane(const T* __restrict__ q, const T* __restrict__ rb, AdjArgs a, int nseg, int ng,
                T* __restrict__ P, FoldOut<T> fo) {
   constexpr int NW = lane_waves<T, D>();
   // a line in LDS, padded so that the NW x (64 / NW) elements a wave stores fall
@@ -786,7 +787,9 @@ __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
   const int nd = D == 0 ? a.nx : (D == 1 ? a.ny : a.nz);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   // consecutive line groups on one XCD: neighbours in x share cache lines
-  const int L = xcd_logical_block(blockIdx.x, gridDim.x), ng = gridDim.x / nseg;
+  const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (b >= ng * nseg) return;
+  const int L = xcd_logical_block(b, ng * nseg);
   const int seg = L / ng, grp = L - seg * ng;
   const int c_lo = seg == 0 ? -3 : LANE_OUT * seg;
   const int c_hi = seg == nseg - 1 ? nd + 3 : LANE_OUT * (seg + 1);
