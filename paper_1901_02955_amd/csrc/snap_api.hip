@@ -734,15 +734,16 @@ unsigned long long* cfl_slots(const snap_grid* g, void* work) {
 // first comes from the reduction kernel; each later one from the previous
 // step's last stage where the kernels can fuse it, else from the kernel.
 // The state flag (the third word) is cleared first; the first stage of every
-// step raises it when its time step is not finite and positive, and where the
-// kernels fuse the reduction the last step also reduces the final state, which
-// a one-thread kernel then checks.
+// step raises it when its time step is not finite and positive, and on 3-D grids
+// whose kernels fuse the reduction the last step also reduces the final state,
+// which a one-thread kernel then checks.
 int rk3_steps_cfl(const snap_grid* g, void* q, double cfl, int nsteps, void* work,
                   double* dt_dev, hipStream_t st) {
   char* w = static_cast<char*>(work);
   unsigned long long* slot = cfl_slots(g, work);
   unsigned long long* flag = slot + 2;
   const bool fused = fused_speed_ok(g);
+  const bool check_last = fused && is3d(g);   // as snap_rk3_steps_status documents
   const CflArgs ca = cfl_args(g);
   if (launch_zero_u64(flag, 1, st)) return device_fail("flag clear launch");
   if (launch_cfl(g->dtype, q, ca, slot, st)) return device_fail("cfl kernel launch");
@@ -751,12 +752,12 @@ int rk3_steps_cfl(const snap_grid* g, void* q, double cfl, int nsteps, void* wor
     unsigned long long* nxt = slot + ((n + 1) & 1);
     const bool more = n + 1 < nsteps;
     const int r = rk3_stages(g, q, 0.0, cur, cfl, dt_dev ? dt_dev + n : nullptr, w, st,
-                             fused ? nxt : nullptr, flag);
+                             fused && (more || check_last) ? nxt : nullptr, flag);
     if (r) return r;
     if (more && !fused && launch_cfl(g->dtype, q, ca, nxt, st))
       return device_fail("cfl kernel launch");
   }
-  if (fused && launch_flag_speed(slot + (nsteps & 1), flag, st))
+  if (check_last && launch_flag_speed(slot + (nsteps & 1), flag, st))
     return device_fail("flag kernel launch");
   return ok();
 }
