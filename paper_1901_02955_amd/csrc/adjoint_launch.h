@@ -19,12 +19,13 @@ inline dim3 lane_grid(long long blocks) {
 template <typename T, int NV, int D, bool HLLC, bool MIX>
 void adj_lane_launch(const T* q, const T* r, const AdjArgs& a, T* P, const FoldOut<T>& fo,
                      hipStream_t st) {
-  constexpr int NW = lane_waves<T, D>();
-  const int nseg = lane_segments(D == 0 ? a.nx : (D == 1 ? a.ny : a.nz));
-  const long long groups = D == 0 ? ((long long)a.ny * a.nz + NW - 1) / NW
-                                  : (long long)((a.nx + NW - 1) / NW) * (D == 1 ? a.nz : a.ny);
-  hipLaunchKernelGGL((k_adj_lane<T, NV, D, HLLC, MIX>), lane_grid(groups * nseg), dim3(64 * NW),
-                     0, st, q, r, a, nseg, (int)groups, P, fo);
+  const int nd = D == 0 ? a.nx : (D == 1 ? a.ny : a.nz);
+  const int nseg = lane_segments(nd), lw = lane_width(nd);
+  const int nlw = lane_waves<T, D>() << (6 - lw);   // lines per workgroup
+  const long long groups = D == 0 ? ((long long)a.ny * a.nz + nlw - 1) / nlw
+                                  : (long long)((a.nx + nlw - 1) / nlw) * (D == 1 ? a.nz : a.ny);
+  hipLaunchKernelGGL((k_adj_lane<T, NV, D, HLLC, MIX>), lane_grid(groups * nseg),
+                     dim3(64 * lane_waves<T, D>()), 0, st, q, r, a, nseg, (int)groups, lw, P, fo);
 }
 
 // The y and z directions march along their lines (k_adj_march) in single

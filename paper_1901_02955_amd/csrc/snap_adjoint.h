@@ -731,18 +731,21 @@ __device__ __forceinline__ void fold_store(const FoldOut<T>& f, const T* __restr
 // r_bar[c-1]) / dx; (3) the WENO5 reverse of its cell (weno5_linrev) and the sum
 // of the five contributions that reach it, in a fixed order: reproducible bit
 // for bit. A wave writes the 54 cells whose contributions it holds whole.
-// y and z lines are loaded and stored through LDS, lane_waves of them
-// consecutive in x per workgroup, so that memory is accessed along x.
+// y and z lines are loaded and stored through LDS, those of a workgroup
+// consecutive in x, so that memory is accessed along x.
 // The x direction overwrites P on every cell of the interior rows (ghosts
 // included); y and z add to it, and overwrite it on the ghost cells beyond
 // their own edges, which they reach first.
 // fo: with fo.fold (z direction, after k_adj_xmerge) a cell at least 3 from the
 // y and z edges is complete here, and its conserved cotangent is formed and
 // stored instead of P (k_adj_consfold then takes the rows that are left).
+// lw: a line takes 2^lw lanes (lane_width), so that a wave holds two lines of up to
+// 22 cells or four of up to 6; what shifts carry across the lines' borders reaches
+// no cell that is written (the halo's two lanes on either side contribute nothing).
 // Blocks: the segments (lane_segments) of the positions -3 .. nd + 2, and in a
-// segment the ng line groups (x: lines (j, k), a line per wave; y, z: groups of
-// lane_waves lines, x fastest), numbered over a grid of one or more rows
-// (lane_grid); the last row's blocks beyond them have nothing to do.
+// segment the ng line groups of lane_waves waves (x: lines (j, k); y, z: groups of
+// consecutive x), numbered over a grid of one or more rows (lane_grid); the last
+// row's blocks beyond them have nothing to do.
 // 256 x 256 x 128, one gradient step in double precision (kept stages): 12.45 ms
 // with tiles of lines in LDS and five barriers per direction, 8.9 ms now; the
 // x direction of 101 x 84 x 64 66 -> 39 us, y 82 -> 55; seven variables on
@@ -757,7 +760,13 @@ __host__ __device__ constexpr int lane_segments(int nd) {
   return (nd + LANE_OUT - 1) / LANE_OUT;
 }
 
-// Lines per workgroup: 32 bytes of every row for y and z. Neighbouring groups
+// log2 of the lanes of a line of nd cells: its padded cells and two lanes beyond
+// either end.
+__host__ __device__ constexpr int lane_width(int nd) {
+  return nd + 10 <= 16 ? 4 : (nd + 10 <= 32 ? 5 : 6);
+}
+
+// Waves per workgroup (one line each from 23 cells on): 32 bytes of every row for y and z. Neighbouring groups
 // meet in one XCD's L2, and small workgroups overlap their barriers: with 64
 // bytes the six-tracer mixture step of 96 x 80 x 64 in double precision took
 // 2078 us against 1889, the gradient of 101 x 84 x 64 3334 against 3237.
@@ -778,7 +787,7 @@ __device__ __forceinline__ double lane_shift(double x, int addr) {
 template <typename T, int NV, int D, bool HLLC, bool MIX>
 __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
     k_adj_lane(const T* __restrict__ q, const T* __restrict__ rb, AdjArgs a, int nseg, int ng,
-               T* __restrict__ P, FoldOut<T> fo) {
+               int lw, T* __restrict__ P, FoldOut<T> fo) {
   constexpr int NW = lane_waves<T, D>();
   // a line in LDS, padded so that the NW x (64 / NW) elements a wave stores fall
   // on different banks
@@ -786,6 +795,7 @@ __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
   __shared__ T S[D == 0 ? 1 : NV][D == 0 ? 1 : NW][D == 0 ? 1 : ROW];
   const int nd = D == 0 ? a.nx : (D == 1 ? a.ny : a.nz);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int pos = lane & ((1 << lw) - 1), lps = 6 - lw;   // lines per wave: 1 << lps
   // consecutive line groups on one XCD: neighbours in x share cache lines
   const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
   if (b >= ng * nseg) return;
@@ -793,20 +803,23 @@ __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
   const int seg = L / ng, grp = L - seg * ng;
   const int c_lo = seg == 0 ? -3 : LANE_OUT * seg;
   const int c_hi = seg == nseg - 1 ? nd + 3 : LANE_OUT * (seg + 1);
-  const int c0 = seg == 0 ? -5 : c_lo - 5;   // the cell of lane 0
-  const int cg = c0 + lane;
+  const int c0 = seg == 0 ? -5 : c_lo - 5;   // the cell of a line's first lane
+  const int cg = c0 + pos;
   const long long sd = D == 0 ? 1 : (D == 1 ? a.sy : a.sz);
   const long long rd = D == 0 ? 1 : (D == 1 ? a.ry : a.rz);
-  // the line this wave computes (lev: its level, x and y lines), and for y and
+  // the line this lane computes (lev: its level, x and y lines), and for y and
   // z the (position, line) this thread loads and stores
-  const int n0 = D == 0 ? a.ny : (a.nx + NW - 1) / NW;   // groups (x: lines) per row
-  const int o1 = D == 0 ? 0 : grp / n0, g0 = (D == 0 ? 0 : grp % n0) * NW;
+  const int nlw = NW << lps;   // lines per workgroup
+  const int n0 = D == 0 ? a.ny : (a.nx + nlw - 1) / nlw;   // groups (x: lines) per row
+  const int o1 = D == 0 ? 0 : grp / n0, g0 = (D == 0 ? 0 : grp % n0) * nlw;
   const long long nl = (long long)a.ny * a.nz;
-  const long long line = D == 0 ? min((long long)grp * NW + wv, nl - 1) : 0;
-  const bool mine = D == 0 ? (long long)grp * NW + wv < nl : true;
+  const long long l0 = (long long)grp * nlw + (threadIdx.x >> lw);
+  const long long line = D == 0 ? min(l0, nl - 1) : 0;
+  const bool mine = D == 0 ? l0 < nl : true;
   const int jx = (int)(D == 0 ? line % a.ny : 0), kx = (int)(D == 0 ? line / a.ny : 0);
-  const int mp = D == 0 ? lane : threadIdx.x / NW, mi = D == 0 ? 0 : g0 + threadIdx.x % NW;
-  const int ml = D == 0 ? 0 : threadIdx.x % NW;
+  const int ml = D == 0 ? 0 : threadIdx.x & (nlw - 1);
+  const int mp = D == 0 ? pos : threadIdx.x / NW >> lps, mi = D == 0 ? 0 : g0 + ml;
+  const int mw = ml >> lps, ms = ((ml & ((1 << lps) - 1)) << lw) + mp;   // its wave and lane
   const int mc = c0 + mp;   // the position this thread loads and stores
   const int lev = D == 0 ? kx : (D == 1 ? o1 : 0);
   const int is = min(mi, a.nx - 1);
@@ -836,13 +849,13 @@ __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
   }
   if constexpr (D != 0) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) S[v][ml][mp] = x[v];
+    for (int v = 0; v < NV; ++v) S[v][mw][ms] = x[v];
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < NV; ++v) x[v] = S[v][wv][lane];
     __syncthreads();
 #pragma unroll
-    for (int v = 0; v < NV; ++v) S[v][ml][mp] = r[v];
+    for (int v = 0; v < NV; ++v) S[v][mw][ms] = r[v];
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < NV; ++v) r[v] = S[v][wv][lane];
@@ -917,12 +930,12 @@ __global__ void __launch_bounds__((64 * lane_waves<T, D>()))
       if (D == 2 && fo.fold && mc >= 3 && mc < nd - 3 && (!a.d3 || (o1 >= 3 && o1 < a.ny - 3))) {
         double pb[NV], acc[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) pb[v] = static_cast<double>(old[v] + S[v][ml][mp]);
+        for (int v = 0; v < NV; ++v) pb[v] = static_cast<double>(old[v] + S[v][mw][ms]);
         adj_cons_from<T, NV, MIX>(q, pb, rb, a, mi, o1, mc, acc);
         fold_store<T, NV>(fo, rb, a, rbo + mc * rd, acc);
       } else {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) p[v * a.sv] = old[v] + S[v][ml][mp];
+        for (int v = 0; v < NV; ++v) p[v * a.sv] = old[v] + S[v][mw][ms];
       }
     }
   }
