@@ -59,11 +59,21 @@ inline bool march_pays(const AdjArgs& a) {
 // The z direction folds the cells at least 3 from the y and z edges, after
 // k_adj_xmerge has added the x copies' cotangents into the cells within 3 of
 // an x edge (the separate fold pass then covers the rows of the 3 lowest and 3
-// highest levels and those within 3 of a y edge); SNAP_ADJ_MARCH_FOLD=0
-// leaves every cell to the fold pass.
-inline bool march_fold_enabled() {
+// highest levels and those within 3 of a y edge), where that takes enough blocks
+// (256 cells of a row) off the fold pass to pay for the merge's launch of 2 to 4 us.
+// Microseconds of a right-hand-side adjoint in double precision without tracers
+// (blocks saved: folded, not): 16x16x16 (100) 39.2, 36.5; 320x1x200 (388) 35.8,
+// 32.8; 40x40x40 (1156) 49.4, 50.1; 16x1x2000 (1994) 31.1, 31.7; 96x80x64 (4292)
+// 150, 159. Not under the mixture, whose fold costs the z kernel what it saves:
+// 96 x 80 x 64 with six tracers in double precision 174 us and 71 for the separate
+// fold, against 219 and 19. SNAP_ADJ_MARCH_FOLD=0 leaves every cell to the fold
+// pass, SNAP_ADJ_MARCH_FOLD=1 folds on every grid that has such cells.
+inline bool fold_pays(const AdjArgs& a) {
+  if (a.nz <= 6) return false;
   const char* e = getenv("SNAP_ADJ_MARCH_FOLD");
-  return !(e && e[0] == '0');
+  if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
+  const long long rows = (long long)(!a.d3 ? 1 : (a.ny > 6 ? a.ny - 6 : 0)) * (a.nz - 6);
+  return rows * ((a.nx + 255) / 256) >= 1024;
 }
 
 // Segment length of the march. A line is cut into as many segments as make the
@@ -118,11 +128,7 @@ int adj_rhs_nv(const AdjWork& w, const AdjArgs& a, const void* q, const void* rb
   // the march addresses each variable's plane with 32-bit byte offsets
   const bool planes_small = a.sv * (long long)sizeof(T) < (1LL << 31) &&
                             a.rv * (long long)sizeof(T) < (1LL << 31);
-  // the z direction folds the cells at least 3 from the y and z edges (not
-  // under the mixture, whose fold costs the z kernel what it saves: 96 x 80 x 64
-  // with six tracers in double precision 174 us and 71 for the separate fold,
-  // against 219 and 19)
-  const bool zfold = march_fold_enabled() && a.nz > 6 && !MIX;
+  const bool zfold = !MIX && fold_pays(a);
   if (zfold) {
     const long long n = (long long)(a.nx > 6 ? 6 : a.nx) * a.ny * a.nz;
     hipLaunchKernelGGL((k_adj_xmerge<T, NV>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,

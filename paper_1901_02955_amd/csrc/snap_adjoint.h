@@ -742,6 +742,9 @@ __device__ __forceinline__ void fold_store(const FoldOut<T>& f, const T* __restr
 // lw: a line takes 2^lw lanes (lane_width), so that a wave holds two lines of up to
 // 22 cells or four of up to 6; what shifts carry across the lines' borders reaches
 // no cell that is written (the halo's two lanes on either side contribute nothing).
+// With a wave to every line 256 x 256 x 4 in double precision took 242 us (tiles of
+// eight lines: 200), now 128; 512 x 512 x 12 1222 us, now 915, and in single
+// precision 632, now 461.
 // Blocks: the segments (lane_segments) of the positions -3 .. nd + 2, and in a
 // segment the ng line groups of lane_waves waves (x: lines (j, k); y, z: groups of
 // consecutive x), numbered over a grid of one or more rows (lane_grid); the last
