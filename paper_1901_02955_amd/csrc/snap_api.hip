@@ -210,7 +210,7 @@ StageArgs stage_args(const snap_grid* g) {
 // Co-resident stage workgroups on the current device (compute units x
 // workgroups per compute unit), cached per device, dtype and variable count;
 // *cus_out (optional) receives the compute-unit count.
-int resident_slots(const snap_grid* g, int* cus_out = nullptr) {
+int resident_slots(const snap_grid* g, bool half, int* cus_out = nullptr) {
   static std::mutex m;
   static std::vector<std::vector<int>> cache;  // [device][key]
   static std::vector<int> cu_count;            // [device]
@@ -218,14 +218,15 @@ int resident_slots(const snap_grid* g, int* cus_out = nullptr) {
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
   const int kind = (is3d(g) && uses_sediment(g)) ? 3
                    : uses_mixture(g) ? 1 : (g->riemann == SNAP_RIEMANN_HLLC ? 2 : 0);
-  const int key = ((g->dtype * 2 + (is3d(g) ? 1 : 0)) * 4 + kind) * 16 + g->ntracer;
+  const int key =
+      (((g->dtype * 2 + (is3d(g) ? 1 : 0)) * 4 + kind) * 16 + g->ntracer) * 2 + (half ? 1 : 0);
   std::lock_guard<std::mutex> lk(m);
   if ((int)cache.size() <= dev) {
     cache.resize(dev + 1);
     cu_count.resize(dev + 1, 0);
   }
   auto& c = cache[dev];
-  if (c.empty()) c.assign(256, 0);
+  if (c.empty()) c.assign(512, 0);
   if (c[key] == 0) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -236,9 +237,11 @@ int resident_slots(const snap_grid* g, int* cus_out = nullptr) {
                                                 : occupancy_sed_f32(g->ntracer))
               : g->dtype == SNAP_F64
                   ? (kind == 1 ? occupancy_mix_f64(g->ntracer, d3)
-                               : kind == 2 ? occupancy_hllc_f64(g->ntracer, d3) : occupancy_f64(g->ntracer, d3))
+                               : kind == 2 ? occupancy_hllc_f64(g->ntracer, d3, half)
+                                           : occupancy_f64(g->ntracer, d3, half))
                   : (kind == 1 ? occupancy_mix_f32(g->ntracer, d3)
-                               : kind == 2 ? occupancy_hllc_f32(g->ntracer, d3) : occupancy_f32(g->ntracer, d3));
+                               : kind == 2 ? occupancy_hllc_f32(g->ntracer, d3, half)
+                                           : occupancy_f32(g->ntracer, d3, half));
     if (per <= 0) per = 1;
     c[key] = cus * per;
     cu_count[dev] = cus;
@@ -287,39 +290,92 @@ bool pass_weights(const snap_grid* g, int passes, double* w) {
   return false;
 }
 
+// Tile of the stage launch over the plane and the number of chunks its levels
+// are split into (3-D). Every chunk pays a warm-up of about one level (two extra
+// vertical reconstructions and primitive loads), and the launch runs in rounds of
+// `slots` co-resident workgroups; the chunk count is the one that minimises
+// rounds x (levels per chunk + 1), the cost.
+struct StageSplit {
+  int tiles_x, tiles_y, chunks, slots;
+  double cost;
+};
+StageSplit stage_split(const snap_grid* g, bool half) {
+  const bool d3 = is3d(g);
+  const TileShape t = g->dtype == SNAP_F64 ? tile_f64(nvar_of(g), d3, uses_mixture(g), half)
+                                           : tile_f32(nvar_of(g), d3, uses_mixture(g), half);
+  StageSplit s;
+  s.tiles_x = (g->nx + t.tx - 1) / t.tx;
+  s.tiles_y = ((d3 ? g->ny : g->nz) + t.ty - 1) / t.ty;
+  s.chunks = 1;
+  s.slots = 0;
+  s.cost = 1e300;
+  if (!d3) return s;
+  s.slots = resident_slots(g, half);
+  const int maxchunk = g->nz / 4 > 1 ? g->nz / 4 : 1;
+  for (int nc = 1; nc <= maxchunk; ++nc) {
+    const int tz = (g->nz + nc - 1) / nc;
+    const long long blocks = (long long)s.tiles_x * s.tiles_y * ((g->nz + tz - 1) / tz);
+    if (blocks > (1LL << 30)) break;
+    const long long rounds = (blocks + s.slots - 1) / s.slots;
+    const double cost = (double)rounds * (tz + 1);
+    if (cost < s.cost - 1e-9) {
+      s.cost = cost;
+      s.chunks = nc;
+    }
+  }
+  return s;
+}
+
+// The 3-D kernels that have a half tile beside the square one (Tile3For).
+bool half_tile(const snap_grid* g) {
+  return is3d(g) && g->dtype == SNAP_F64 && !uses_mixture(g) && g->ntracer >= 2 && g->ntracer <= 4;
+}
+
+// Whether the half tile is the faster one. Microseconds per SSP-RK3 step, square
+// and half, two, three and four tracers (LMARS):
+//   more than one workgroup per compute unit: by rounds and levels, of which the
+//   square tile's take 1.4 times as long, with four tracers 1.75 times:
+//     100x100x100 (cost 0.52 of the half tile's) 367, 497; 446, 551; 587, 602
+//     256x20x128 (0.64) 304, 343; 361, 381; 457, 415
+//     160x24x80 (0.83) 174, 159; 204, 175; 255, 191
+//     500x8x200 (1) 418, 369; 469, 420; 609, 469
+//   at most one: the square tile (200x12x64 125, 133; 135, 146; 143, 159), but not
+//   where the last tile has up to four columns, which take its four waves longer than
+//   full ones take them: 32x31x33 151, 150; 178, 177 (two, four), 33x31x33 230, 148;
+//   282, 176, 36x31x33 158, 149; 183, 176, 38x31x33 151, 149; 177, 175.
+// SNAP_STAGE_HALF=0 or 1 overrides the rule.
+bool half_pays(const snap_grid* g, const StageSplit& sq, const StageSplit& half) {
+  const char* e = getenv("SNAP_STAGE_HALF");
+  if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
+  int cus = 0;
+  resident_slots(g, false, &cus);
+  const int tz = (g->nz + sq.chunks - 1) / sq.chunks;
+  if ((long long)sq.tiles_x * sq.tiles_y * ((g->nz + tz - 1) / tz) <= cus)
+    return (g->nx - 1) % 16 < 4;
+  return sq.cost * (g->ntracer == 4 ? 1.75 : 1.4) > half.cost;
+}
+
 // Tiling of the stage launch; returns the number of workgroups.
 int stage_tiling(const snap_grid* g, StageArgs& a) {
   const bool d3 = is3d(g);
-  const TileShape t = g->dtype == SNAP_F64 ? tile_f64(nvar_of(g), d3, uses_mixture(g))
-                                           : tile_f32(nvar_of(g), d3, uses_mixture(g));
-  a.tiles_x = (g->nx + t.tx - 1) / t.tx;
+  StageSplit sp = stage_split(g, false);
+  a.half = 0;
+  if (half_tile(g)) {
+    const StageSplit f = stage_split(g, true);
+    if (half_pays(g, sp, f)) {
+      sp = f;
+      a.half = 1;
+    }
+  }
+  a.tiles_x = sp.tiles_x;
+  a.tiles_y = sp.tiles_y;
   if (!d3) {
-    a.tiles_y = (g->nz + t.ty - 1) / t.ty;
     a.nchunk = 1;
     a.tz = g->nz;
     return a.tiles_x * a.tiles_y;
   }
-  a.tiles_y = (g->ny + t.ty - 1) / t.ty;
-  const int tiles = a.tiles_x * a.tiles_y;
-  // Split the levels into chunks. Every chunk pays a warm-up of about one
-  // level (two extra vertical reconstructions and primitive loads), and the
-  // launch runs in rounds of `slots` co-resident workgroups; pick the chunk
-  // count that minimises rounds x (levels per chunk + 1).
-  const int slots = resident_slots(g);
-  int best = 1;
-  double best_cost = 1e300;
-  const int maxchunk = g->nz / 4 > 1 ? g->nz / 4 : 1;
-  for (int nc = 1; nc <= maxchunk; ++nc) {
-    const int tz = (g->nz + nc - 1) / nc;
-    const long long blocks = (long long)tiles * ((g->nz + tz - 1) / tz);
-    if (blocks > (1LL << 30)) break;
-    const long long rounds = (blocks + slots - 1) / slots;
-    const double cost = (double)rounds * (tz + 1);
-    if (cost < best_cost - 1e-9) {
-      best_cost = cost;
-      best = nc;
-    }
-  }
+  const int tiles = a.tiles_x * a.tiles_y, slots = sp.slots;
+  int best = sp.chunks;
   if (const char* env = getenv("SNAP_STAGE_CHUNKS")) {
     const int nc = atoi(env);
     if (nc >= 1) best = nc < g->nz ? nc : g->nz;
@@ -329,7 +385,7 @@ int stage_tiling(const snap_grid* g, StageArgs& a) {
   // One workgroup per compute unit per chunk, all resident at once: chunk c is
   // dispatch pass c, and its level range is sized by that pass's speed.
   int cus = 0;
-  resident_slots(g, &cus);
+  resident_slots(g, a.half != 0, &cus);
   a.low = (long long)tiles * a.nchunk <= cus ? 1 : 0;
   double w[SNAP_MAX_PASSES];
   a.pass_map = 0;

@@ -69,18 +69,19 @@ struct SumArgs {
 };
 
 // Tile shape of the stage kernels for an element size, variable count, 2-D or
-// 3-D, and equation of state.
+// 3-D, and equation of state; half: of the 3-D kernels that have two, the
+// smaller.
 struct TileShape {
   int tx, ty;
 };
-TileShape tile_f64(int nv, bool d3, bool mix);
-TileShape tile_f32(int nv, bool d3, bool mix);
-int occupancy_f64(int ntracer, bool d3);
-int occupancy_f32(int ntracer, bool d3);
+TileShape tile_f64(int nv, bool d3, bool mix, bool half);
+TileShape tile_f32(int nv, bool d3, bool mix, bool half);
+int occupancy_f64(int ntracer, bool d3, bool half);
+int occupancy_f32(int ntracer, bool d3, bool half);
 int occupancy_mix_f64(int ntracer, bool d3);
 int occupancy_mix_f32(int ntracer, bool d3);
-int occupancy_hllc_f64(int ntracer, bool d3);
-int occupancy_hllc_f32(int ntracer, bool d3);
+int occupancy_hllc_f64(int ntracer, bool d3, bool half);
+int occupancy_hllc_f32(int ntracer, bool d3, bool half);
 
 struct AdjArgs;
 

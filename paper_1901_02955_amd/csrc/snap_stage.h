@@ -93,6 +93,7 @@ struct StageArgs {
   unsigned long long* state_flag;
   // 3-D only: at most one workgroup per compute unit (Stage3DShape's LOW)
   int low;
+  int half;   // 3-D only: the half tile where the kernel has one (Tile3For)
   // 1: q holds rho - rhobar_k and E - pbar_k / (gamma - 1) (perturbation
   // storage, passive tracers only); 0: the full conserved state.
   int pert;
@@ -1137,7 +1138,7 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
   };
 
   constexpr int ND = two_sided<T, NV, MIX, true>();
-  constexpr bool PACK = Stage3DShape<T, NT, MIX, SED, LOW>::pack;
+  constexpr bool PACK = Stage3DShape<T, NT, MIX, SED, LOW>::pack && TX == TY;
   constexpr bool TAN = upwind_tangential<T, ND, MIX, HLLC, PACK>();
   constexpr int N2 = TAN ? 3 : ND;
   T W[5][NV];     // primitives of levels s-1 .. s+3 (own column)

@@ -7,6 +7,8 @@ int launch_stage_hllc_f64(int ntracer, bool d3, StageArgs a, int nblocks, hipStr
   return launch_stage_t<double, false, true>(ntracer, d3, a, nblocks, st);
 }
 
-int occupancy_hllc_f64(int ntracer, bool d3) { return occupancy_t<double, false, true>(ntracer, d3); }
+int occupancy_hllc_f64(int ntracer, bool d3, bool half) {
+  return occupancy_t<double, false, true>(ntracer, d3, half);
+}
 
 }  // namespace snap

@@ -34,6 +34,9 @@ struct Tile3For {
   static constexpr bool SQ = !MIX && sizeof(Plane<T, 5 + NT, 16, 16>) <= 80 * 1024;
   static constexpr int TX = SQ ? 16 : TileFor<T, NT>::TX;
   static constexpr int TY = SQ ? 16 : TileFor<T, NT>::TY;
+  // half: the smaller tile of TileFor is there too (StageArgs::half), for the
+  // domains that the square one pads more (half_pays)
+  static constexpr bool half = TX != TileFor<T, NT>::TX || TY != TileFor<T, NT>::TY;
 };
 
 // MIX: the mixture equation of state (instantiated for NT >= 1 only; with no
@@ -45,7 +48,11 @@ int launch_nt(bool d3, const StageArgs& a, int nblocks, hipStream_t st) {
   constexpr bool M = MIX && NT > 0;
   constexpr int TX3 = Tile3For<T, NT, M>::TX, TY3 = Tile3For<T, NT, M>::TY;
   constexpr bool LOW = Stage3DShape<T, NT, M, false>::has_low;
-  if (d3 && LOW && a.low)
+  constexpr bool HALF = Tile3For<T, NT, M>::half;
+  if (d3 && HALF && a.half)
+    hipLaunchKernelGGL((k_stage3d<T, NT, TX, TY, M, HLLC, false, HALF>), dim3(nblocks),
+                       dim3(TX * TY), 0, st, a);
+  else if (d3 && LOW && a.low)
     hipLaunchKernelGGL((k_stage3d<T, NT, TX3, TY3, M, HLLC, false, LOW>), dim3(nblocks),
                        dim3(TX3 * TY3), 0, st, a);
   else if (d3)
@@ -58,14 +65,18 @@ int launch_nt(bool d3, const StageArgs& a, int nblocks, hipStream_t st) {
 }
 
 template <typename T, int NT, bool MIX, bool HLLC = false>
-int occupancy_nt(bool d3) {
+int occupancy_nt(bool d3, bool half = false) {
   constexpr int TX = TileFor<T, NT>::TX, TY = TileFor<T, NT>::TY;
   constexpr bool M = MIX && NT > 0;
   constexpr int TX3 = Tile3For<T, NT, M>::TX, TY3 = Tile3For<T, NT, M>::TY;
+  constexpr bool HALF = Tile3For<T, NT, M>::half;
   int n = 0;
-  const void* k = d3 ? reinterpret_cast<const void*>(&k_stage3d<T, NT, TX3, TY3, M, HLLC>)
-                     : reinterpret_cast<const void*>(&k_stage2d<T, NT, TX, TY, M, HLLC>);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, d3 ? TX3 * TY3 : TX * TY, 0) !=
+  const bool f = HALF && d3 && half;
+  const void* k =
+      f    ? reinterpret_cast<const void*>(&k_stage3d<T, NT, TX, TY, M, HLLC, false, HALF>)
+      : d3 ? reinterpret_cast<const void*>(&k_stage3d<T, NT, TX3, TY3, M, HLLC>)
+           : reinterpret_cast<const void*>(&k_stage2d<T, NT, TX, TY, M, HLLC>);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, d3 && !f ? TX3 * TY3 : TX * TY, 0) !=
       hipSuccess)
     return 0;
   return n;
@@ -142,17 +153,17 @@ int occupancy_dry(bool hllc, bool d3) {
 
 // Workgroups of the stage kernel that fit on one compute unit (0 if unknown).
 template <typename T, bool MIX, bool HLLC = false>
-int occupancy_t(int ntracer, bool d3) {
+int occupancy_t(int ntracer, bool d3, bool half) {
   switch (ntracer) {
     case 0: return occupancy_dry<T>(HLLC, d3);
-    case 1: return occupancy_nt<T, 1, MIX, HLLC>(d3);
-    case 2: return occupancy_nt<T, 2, MIX, HLLC>(d3);
-    case 3: return occupancy_nt<T, 3, MIX, HLLC>(d3);
-    case 4: return occupancy_nt<T, 4, MIX, HLLC>(d3);
-    case 5: return occupancy_nt<T, 5, MIX, HLLC>(d3);
-    case 6: return occupancy_nt<T, 6, MIX, HLLC>(d3);
-    case 7: return occupancy_nt<T, 7, MIX, HLLC>(d3);
-    case 8: return occupancy_nt<T, 8, MIX, HLLC>(d3);
+    case 1: return occupancy_nt<T, 1, MIX, HLLC>(d3, half);
+    case 2: return occupancy_nt<T, 2, MIX, HLLC>(d3, half);
+    case 3: return occupancy_nt<T, 3, MIX, HLLC>(d3, half);
+    case 4: return occupancy_nt<T, 4, MIX, HLLC>(d3, half);
+    case 5: return occupancy_nt<T, 5, MIX, HLLC>(d3, half);
+    case 6: return occupancy_nt<T, 6, MIX, HLLC>(d3, half);
+    case 7: return occupancy_nt<T, 7, MIX, HLLC>(d3, half);
+    case 8: return occupancy_nt<T, 8, MIX, HLLC>(d3, half);
     default: return 0;
   }
 }
@@ -174,24 +185,24 @@ int launch_stage_t(int ntracer, bool d3, const StageArgs& a, int nblocks, hipStr
 }
 
 template <typename T, int NT>
-TileShape tile_nt(bool d3, bool mix) {
+TileShape tile_nt(bool d3, bool mix, bool half) {
   using P = Tile3For<T, NT, false>;
   using F = TileFor<T, NT>;
-  return d3 && !mix ? TileShape{P::TX, P::TY} : TileShape{F::TX, F::TY};
+  return d3 && !mix && !half ? TileShape{P::TX, P::TY} : TileShape{F::TX, F::TY};
 }
 
 template <typename T>
-TileShape tile_t(int nv, bool d3, bool mix) {
+TileShape tile_t(int nv, bool d3, bool mix, bool half) {
   switch (nv - 5) {
-    case 0: return tile_nt<T, 0>(d3, mix);
-    case 1: return tile_nt<T, 1>(d3, mix);
-    case 2: return tile_nt<T, 2>(d3, mix);
-    case 3: return tile_nt<T, 3>(d3, mix);
-    case 4: return tile_nt<T, 4>(d3, mix);
-    case 5: return tile_nt<T, 5>(d3, mix);
-    case 6: return tile_nt<T, 6>(d3, mix);
-    case 7: return tile_nt<T, 7>(d3, mix);
-    default: return tile_nt<T, 8>(d3, mix);
+    case 0: return tile_nt<T, 0>(d3, mix, half);
+    case 1: return tile_nt<T, 1>(d3, mix, half);
+    case 2: return tile_nt<T, 2>(d3, mix, half);
+    case 3: return tile_nt<T, 3>(d3, mix, half);
+    case 4: return tile_nt<T, 4>(d3, mix, half);
+    case 5: return tile_nt<T, 5>(d3, mix, half);
+    case 6: return tile_nt<T, 6>(d3, mix, half);
+    case 7: return tile_nt<T, 7>(d3, mix, half);
+    default: return tile_nt<T, 8>(d3, mix, half);
   }
 }
 

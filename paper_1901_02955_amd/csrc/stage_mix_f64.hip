@@ -7,6 +7,6 @@ int launch_stage_mix_f64(int ntracer, bool d3, StageArgs a, int nblocks, hipStre
   return launch_stage_t<double, true>(ntracer, d3, a, nblocks, st);
 }
 
-int occupancy_mix_f64(int ntracer, bool d3) { return occupancy_t<double, true>(ntracer, d3); }
+int occupancy_mix_f64(int ntracer, bool d3) { return occupancy_t<double, true>(ntracer, d3, false); }
 
 }  // namespace snap
