@@ -1432,12 +1432,13 @@ __global__ void __launch_bounds__(TX* TY, (Stage3DShape<T, NT, MIX, SED, LOW>::w
 // axis. Shared by the single-domain kernel and the batched (ensemble) kernel.
 // Small domains are bound by launches and latency, so a step is three launches:
 // ghost values are read at their sources (GF_ON) and the last stage reduces the
-// next step's signal speed. With three fills and the reduction's two launches
+// next step's signal speed (SPEED: not in a batch, whose time steps come from the
+// host). With three fills and the reduction's two launches
 // beside them a device-dt step of 64 x 64 cells in double precision took 43 us,
 // without them 27 us; a batched step of 64 domains (50 368 cells on average)
 // in single precision 386 -> 371 us.
 // ---------------------------------------------------------------------------
-template <typename T, int NT, int TX, int TZ, bool MIX = false, bool HLLC = false>
+template <typename T, int NT, int TX, int TZ, bool MIX, bool HLLC, bool SPEED>
 __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
                                              Plane<T, 5 + NT, TX, TZ>& S) {
   constexpr int NV = 5 + NT;
@@ -1524,7 +1525,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
     R[4] = R[4] - grav * qs[po + 3 * a.sv];
     const long long ro = (long long)k * a.rz + i;
     write_cell<T, NV>(a, qs, po, ro, R);
-    if constexpr (!MIX) {
+    if constexpr (SPEED) {
       if (a.smax_out != nullptr)
         smx = speed_bits_2d<T, NV>(a, R, a.pert ? a.rbar_c[k + NG] : 0.0,
                                    a.pert ? a.pbar_c[k + NG] : 0.0);
@@ -1532,7 +1533,7 @@ __device__ __forceinline__ void stage2d_tile(const StageArgs& a, int L,
   }
   // the next step's signal speed: one atomic per wave, and none where the
   // running maximum (read once, perhaps stale, never too large) already covers it
-  if constexpr (!MIX) {
+  if constexpr (SPEED) {
     if (a.smax_out != nullptr) {
       for (int off = 32; off > 0; off >>= 1) {
         const unsigned long long o2 = __shfl_xor(smx, off, 64);
@@ -1550,7 +1551,7 @@ __global__ void __launch_bounds__(TX* TZ) k_stage2d(StageArgs a) {
   __shared__ Plane<T, 5 + NT, TX, TZ> S;
   store_stage_dt(a, stage_dt(a));
   if (a.smax_zero != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.smax_zero = 0ULL;
-  stage2d_tile<T, NT, TX, TZ, MIX, HLLC>(a, xcd_logical_block(blockIdx.x, gridDim.x), S);
+  stage2d_tile<T, NT, TX, TZ, MIX, HLLC, !MIX>(a, xcd_logical_block(blockIdx.x, gridDim.x), S);
 }
 
 // Ensemble of 2-D domains in one persistent launch: work item w is tile
@@ -1558,8 +1559,14 @@ __global__ void __launch_bounds__(TX* TZ) k_stage2d(StageArgs a) {
 // items w = blockIdx.x, blockIdx.x + gridDim.x, ... A barrier closes every tile:
 // its last phase still reads the primitive plane (density perturbation for the
 // gravity source) that the next tile's first phase overwrites.
+// The single-precision instances of 32 x 8 and 8 x 32 cells are held to six waves per
+// SIMD, which they held before they read ghosts in place (82 and 95 registers).
+template <typename T, int NT, int TX, int TZ>
+constexpr int batch_waves() {
+  return sizeof(T) == 4 && NT == 0 && TX * TZ == 256 && (TX == 8 || TZ == 8) ? 6 : 1;
+}
 template <typename T, int NT, int TX, int TZ, bool MIX = false, bool HLLC = false>
-__global__ void __launch_bounds__(TX* TZ) k_stage2d_batched(const StageArgs* __restrict__ descs,
+__global__ void __launch_bounds__(TX* TZ, (batch_waves<T, NT, TX, TZ>())) k_stage2d_batched(const StageArgs* __restrict__ descs,
                                                             const int* __restrict__ first, int n) {
   __shared__ Plane<T, 5 + NT, TX, TZ> S;
   const int total = first[n];
@@ -1573,7 +1580,7 @@ __global__ void __launch_bounds__(TX* TZ) k_stage2d_batched(const StageArgs* __r
         hi = mid;
     }
     const StageArgs a = descs[lo];
-    stage2d_tile<T, NT, TX, TZ, MIX, HLLC>(a, w - first[lo], S);
+    stage2d_tile<T, NT, TX, TZ, MIX, HLLC, false>(a, w - first[lo], S);
     __syncthreads();
   }
 }
