@@ -386,7 +386,7 @@ int stage_tiling(const snap_grid* g, StageArgs& a) {
   // dispatch pass c, and its level range is sized by that pass's speed.
   int cus = 0;
   resident_slots(g, a.half != 0, &cus);
-  a.low = (long long)tiles * a.nchunk <= cus ? 1 : 0;
+  a.low = (long long)tiles * a.nchunk <= (g->dtype == SNAP_F32 ? 2LL : 1LL) * cus ? 1 : 0;
   double w[SNAP_MAX_PASSES];
   a.pass_map = 0;
   if (tiles == cus && tiles % 8 == 0 && (long long)tiles * a.nchunk == slots &&

@@ -91,7 +91,7 @@ struct StageArgs {
   // that time step is not finite and positive, i.e. the reduced state had a
   // non-finite or non-positive density or pressure somewhere.
   unsigned long long* state_flag;
-  // 3-D only: at most one workgroup per compute unit (Stage3DShape's LOW)
+  // 3-D only: no more workgroups than Stage3DShape's LOW instances run at once
   int low;
   int half;   // 3-D only: the half tile where the kernel has one (Tile3For)
   // 1: q holds rho - rhobar_k and E - pbar_k / (gamma - 1) (perturbation
@@ -1016,15 +1016,19 @@ __device__ __forceinline__ void cons_to_prim_t(const T (&c)[NV], const LevelRef&
 // sedimentation instances load nothing ahead, which makes room for their fall
 // fluxes, and are held to two waves; packed from six tracers on, where they
 // spilled (moist step with six tracers on 160 x 144 x 96: 1020 -> 961 us).
-// LOW: a launch of at most one workgroup per compute unit, which more waves per
-// SIMD do not help: the instances whose held registers spill leave them alone
-// there (75 x 60 x 40, double precision, 3 tracers: 187 held, 175 us).
+// LOW: a launch that more waves per SIMD do not help, of at most one workgroup per
+// compute unit, or two in single precision, where the registers left alone hold two
+// waves: the instances whose held registers spill, that gave up the loads ahead for
+// a wave, or that are packed leave all that there (75 x 60 x 40, double precision, 3
+// tracers: 187 us held, 175; single precision with 2 to 5 tracers, held and not:
+// 40 x 40 x 40 with 4 tracers 130, 123; 200 x 4 x 100, 1.3 workgroups per compute unit,
+// 105, 103; 112, 110; 124, 118; 136, 127).
 template <typename T, int NT, bool MIX, bool SED, bool LOW = false>
 struct Stage3DShape {
   static constexpr bool F32 = sizeof(T) == 4;
   static constexpr bool pack = SED   ? F32 && NT >= 6
                                : MIX ? F32 && (NT == 6 || NT == 8)
-                               : F32 ? NT == 4 || (NT == 5 && !LOW)
+                               : F32 ? (NT == 4 || NT == 5) && !LOW
                                      : NT >= 2 && NT <= 4;
   static constexpr bool ahead =
       !SED && (F32 ? NT <= 6 && (MIX || NT == 0 || NT == 6 || LOW) : NT == 0);
@@ -1034,10 +1038,8 @@ struct Stage3DShape {
                                : F32 && NT >= 1 && NT <= 5 ? 3
                                : !F32 && NT >= 2 && NT <= 4 ? 2
                                                       : 1;
-  // the held instances that spill or gave up the loads ahead for a wave, for which
-  // a LOW one exists (right-hand side of 40 x 40 x 40, HLLC, two tracers, single
-  // precision: 37.9 -> 36.6 us)
-  static constexpr bool has_low = !MIX && !SED && (F32 ? NT == 2 || NT == 3 || NT == 5 : NT == 3 || NT == 4);
+  // the instances for which a LOW one exists
+  static constexpr bool has_low = !MIX && !SED && (F32 ? NT >= 2 && NT <= 5 : NT == 3 || NT == 4);
 };
 template <typename T, int NT, int TX, int TY, bool MIX = false, bool HLLC = false,
           bool SED = false, bool LOW = false>
