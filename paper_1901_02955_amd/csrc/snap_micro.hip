@@ -25,21 +25,28 @@ __device__ __forceinline__ void set_tracer(double (&c)[NV], int idx, double val)
 // The kernels over single cells take 256 consecutive cells of a level per block
 // (the rows of a level follow one another, so that only a level's last wave is
 // not full: with a block per row, 160 cells leave a sixth of the lanes of its
-// waves idle and 96 a quarter). A launch holds fewer than 2^32 threads along x,
-// which a state of 2^32 cells and less can reach, and 65535 blocks along y and z:
-// the levels lie along y and, beyond LEVELS_Y of them, z.
-constexpr int LEVELS_Y = 32768;
+// waves idle and 96 a quarter). A launch holds fewer than 2^32 threads along an
+// axis, which a state of some 2^32 cells in the card's memory passes: levels beyond
+// 2^23 blocks lie along the second axis. (Not with the grid's size read in the
+// kernel, which costs every call 0.3 us.)
+template <typename A>
+__host__ __device__ inline unsigned micro_blocks(const A& a) {   // of a level
+  return (unsigned)(((long long)a.nx * a.ny + 255) / 256);
+}
+__host__ __device__ inline unsigned micro_levels(unsigned per) {   // of a row of the grid
+  return per < (1u << 23) ? (1u << 23) / per : 1u;
+}
 template <typename A>
 dim3 micro_grid(const A& a) {
-  const int ly = a.nz < LEVELS_Y ? a.nz : LEVELS_Y;
-  return dim3((unsigned)(((long long)a.nx * a.ny + 255) / 256), (unsigned)ly,
-              (unsigned)((a.nz + ly - 1) / ly));
+  const unsigned per = micro_blocks(a), lev = micro_levels(per), nz = (unsigned)a.nz;
+  return dim3(per * (nz < lev ? nz : lev), (nz + lev - 1) / lev);
 }
 template <typename A>
 __device__ __forceinline__ bool micro_cell(const A& a, int& i, int& j, int& k) {
-  const unsigned plane = (unsigned)a.nx * a.ny;   // below 2^32 for any state in memory
-  const unsigned c = blockIdx.x * 256 + threadIdx.x;
-  k = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+  const unsigned plane = (unsigned)a.nx * a.ny, per = (plane + 255) / 256;
+  k = (int)(blockIdx.x / per);
+  const unsigned c = (blockIdx.x - (unsigned)k * per) * 256 + threadIdx.x;
+  if (blockIdx.y != 0) k += (int)(blockIdx.y * micro_levels(per));
   j = (int)(c / (unsigned)a.nx);
   i = (int)(c - (unsigned)j * a.nx);
   return c < plane && k < a.nz;
