@@ -61,7 +61,10 @@ def algorithmic_flops_per_cell_stage(ntracer: int, ndir: int, mixture: bool = Fa
     Counted from the method's formulas (+, -, *, /, sqrt = 1 flop each, a fused
     multiply-add = 2), with no halo redundancy, address arithmetic or data
     movement: conserved -> primitive 14 + NT; WENO5 per variable and direction
-    (both faces of the cell, shared smoothness indicators) 78; LMARS per face
+    78 where a face's flux takes both its sides (both faces of the cell, shared
+    smoothness indicators) and 55 where it takes the upwind side only (one value
+    per face): density, normal velocity and pressure, under the mixture also the
+    tracers, against the two tangential velocities and passive tracers; LMARS per face
     37 + NT; divergence 3 per variable and direction; gravity 4; Runge-Kutta
     combination 4 per variable averaged over the three stages. The mixture
     equation of state adds 6 NT + 2 to conserved -> primitive (chemical
@@ -73,8 +76,11 @@ def algorithmic_flops_per_cell_stage(ntracer: int, ndir: int, mixture: bool = Fa
     """
     nv = 5 + ntracer
     face = (66 + 3 * ntracer) if hllc else (37 + ntracer)
-    n = (14 + ntracer) + ndir * nv * 78 + ndir * face + ndir * 3 * nv + 4 + 4 * nv
-    if mixture and ntracer > 0:
+    mixed = mixture and ntracer > 0
+    two_sided = 3 + (ntracer if mixed else 0)
+    weno = 78 * two_sided + 55 * (nv - two_sided)
+    n = (14 + ntracer) + ndir * weno + ndir * face + ndir * 3 * nv + 4 + 4 * nv
+    if mixed:
         n += 6 * ntracer + 2 + ndir * (12 * ntracer + 10)
     return n
 
