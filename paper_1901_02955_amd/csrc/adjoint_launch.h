@@ -47,6 +47,10 @@ constexpr bool march_fits() {
 // 5 variables 96x96x48 486, 376; 160x160x80 1247, 1172; 192x160x96 (six steps)
 // 6881, 6652; 256x256x128 4002, 4580;
 // 7 variables 96x96x48 637, 489; 160x160x80 1674, 1612; 256x256x128 5850, 6575.
+// Of one right-hand-side adjoint, 5 and 7 variables: 200x200x110 (4.4e6 cells) 517,
+// 538; 729, 797. The line lies between those sizes. Flat grids would cross
+// over earlier (512x512x12, 3.1e6: 383, 461; 300x24x300, 2.2e6: 288, 318), narrow
+// ones later (24x300x300, 2.2e6: 381, 338), which the rule leaves out.
 // (read at every launch, so that a process can compare both kernels)
 inline bool march_pays(const AdjArgs& a) {
   const char* e = getenv("SNAP_ADJ_MARCH");

@@ -116,8 +116,12 @@ __device__ __forceinline__ LevelRef level_ref(int pert, double rbar, double pbar
 enum : int { GF_ON = 1, GF_RX = 2, GF_RY = 4, GF_RZ = 8 };
 
 // The 3-D stage kernels that can read ghosts in place (GF_ON): those without
-// tracers. With tracers the extra per-level scalar work pushed some instances
-// past an occupancy step, and they keep the fill. (The 2-D kernels all can.)
+// tracers. The others keep the fill. Some have the registers for it by now (as
+// compiled, with the fill and without: mixture in single precision with four
+// tracers 237, 239, with six 243, 245, with rain 227, 229; passive with two 160,
+// 167, with four 165, 167), while others would spill more (passive with three and
+// five in single precision, with four in double); none has been timed without it.
+// (The 2-D kernels all can.)
 constexpr bool ghosts_in_place(int ntracer) { return ntracer == 0; }
 
 // 3-D kernels that can reduce the signal speed of their output (smax_out).
@@ -262,12 +266,15 @@ constexpr int two_sided() {
 // of both sides, so those three are reconstructed per cell, and the two others
 // per face once its side is known: two of five two-sided reconstructions become
 // one-sided, for five more reads of the plane (registers selected in z) per
-// face. 256 x 256 x 128, four steps: 6365 -> 6156 us; 75 x 60 x 40 129 -> 126;
-// one to eight tracers on 256 x 192 x 96 within 0 to 1.5 %. Single precision,
-// at the edge of three waves per SIMD (155 -> 167 registers), took 2301 -> 2817
-// us (250 x 187 x 101, four steps), and the 2-D kernels, where every wave is
-// waited for, 718 -> 735 (256 x 256, twenty steps): they keep both sides, as do
-// HLLC and the mixture.
+// face. 256 x 256 x 128, four steps: 6365 -> 6156 us; 75 x 60 x 40 129 -> 126; with
+// tracers, where not packed, within 0 to 1.5 % on 256 x 192 x 96. Not in single
+// precision: the dry instance takes 171 registers under the scheduling of
+// its file, which is two waves per SIMD instead of three (2301 -> 2817 us, 250 x 187
+// x 101, four steps). Held to three waves it compiles to 161 without spills, a form
+// that has not been timed. Not in the 2-D kernels: one domain of 256 x 256, where
+// every wave is waited for, took 718 -> 735 us in twenty steps, the batch of 64 in
+// single precision 1.1 % longer (80 -> 82 registers, six waves to five, in the
+// kernel of that time). HLLC and the mixture keep both sides, too; neither was tried.
 template <typename T, int ND, bool MIX, bool HLLC, bool PACK>
 constexpr bool upwind_tangential() {
   return sizeof(T) == 8 && ND == 5 && !MIX && !HLLC && !PACK;
@@ -500,11 +507,6 @@ __device__ __forceinline__ void phase_reconstruct(Plane<T, NV, TX, TY>& S, int w
   }
 }
 
-// Phase L: LMARS at every face of the tile, by the item that holds its right
-// state. x faces use the reference of their row (xref); second-axis faces use
-// sref(face index). SNRM is the index of the second axis's velocity; the flux
-// is called in two branches, each with a constant normal, so that picking the
-// normal velocity and adding p* need no selects over the velocity components.
 // The upwind value of one variable at a face between cells c-1 and c of a line
 // of the plane: cells c-3 .. c+1 in order from the left side, c+2 .. c-2 from
 // the right, so the side only picks the five addresses (lo: cell c-3, stride st).
@@ -522,12 +524,16 @@ struct UpwindStencil {
   }
 };
 
+// Phase L: the flux at every face of the tile, by the item that holds its right
+// state. x faces use the reference of their row (xref); second-axis faces use
+// sref(face index). SNRM is the index of the second axis's velocity; the flux
+// is called in two branches, each with a constant normal, so that picking the
+// normal velocity and adding p* need no selects over the velocity components.
 // Passive tracers: once a face's flux is known, so is its upwind side, and the
 // item reconstructs each tracer there from the plane (UpwindStencil) and
-// multiplies by the mass flux. Against the
-// two-sided reconstruction of every cell it saves a fifth of the WENO
-// instructions, the face states' way through LDS and the right states'
-// registers.
+// multiplies by the mass flux. Against the two-sided reconstruction of every cell
+// it saves a fifth of the WENO instructions, the face states' way through LDS and
+// the right states' registers.
 template <typename T, int NV, int ND, int TX, int TY, int SNRM, bool MIX, bool HLLC,
           typename XRef, typename SRef>
 __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int h, T eps,
@@ -552,7 +558,8 @@ __device__ __forceinline__ void phase_lmars(Plane<T, NV, TX, TY>& S, int w, int 
       // 2-D: the face's references are loaded ahead of the branch, both axes in one
       // go (64 x 64, double precision, 20 steps: 547 -> 540 us; 256 x 256 724 ->
       // 708). Not HLLC, whose instances of other tile shapes then contract
-      // differently: 1.8e-6 apart in single precision
+      // differently: 1.8e-6 apart in single precision. Not the mixture, for which it
+      // was not measured
       constexpr bool REF = SNRM == 3 && !HLLC && !MIX;
       if constexpr (REF) {
         if (xa)
