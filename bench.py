@@ -469,7 +469,7 @@ def run_ensemble(steps: int, repeats: int = 5):
             "batched_value": cells * steps / tb, "separate_value": cells * steps / ts,
             "unit": "cell-updates/s", "batched_ms_per_step": tb / steps * 1e3,
             "separate_ms_per_step": ts / steps * 1e3, "speedup": ts / tb,
-            "launches_per_step": {"batched": 6, "separate": 6 * len(grids)},
+            "launches_per_step": {"batched": 3, "separate": 3 * len(grids)},
             "tuned": {k: tuned[k] for k in ("variant", "tile", "nblocks")}}
 
 
